@@ -680,8 +680,11 @@ rgcn_status rgcn_block_backward_dense(const rgcn_block *block, const rgcn_params
                             nd > 0 ? dy[t] : nullptr, hilo, L.d_out, out,
                             (float *)(scratch + L.off_partial), stream), "weight gradient");
         if (dbias && dbias[t])
+            // the weight-gradient partials are reduced by now: their space and the column
+            // sums' own behind it serve the row ranges' sums
             TRY_HIP(column_sums(nd > 0 ? dy[t] : nullptr, hilo, nd, L.d_out, dbias[t],
-                                (float *)(scratch + L.off_colsum), 0, stream), "bias gradient");
+                                (float *)(scratch + L.off_partial),
+                                L.off_split_partial - L.off_partial, stream), "bias gradient");
         // input side: dMs_t = dY_t [W_self_t | W_r ...]^T, relation slots divided by deg
         if (nd > 0 && L.dms_nslots[t] > 0) {
             DmsSlots ds{};

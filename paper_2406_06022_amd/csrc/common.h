@@ -308,9 +308,11 @@ hipError_t featureless_mean(const FeatArgs &a, uint32_t *words, hipStream_t s);
 
 hipError_t pack_weights(rgcn_dtype dt, int d_in, int d_out, const void *const *w_slots,
                         int nslots, void *wcat_t, hipStream_t s);
-// hilo: dy rows in the hi/lo form (cols bf16 high parts, then cols low parts)
+// hilo: dy rows in the hi/lo form (cols bf16 high parts, then cols low parts); cols a
+// multiple of 4, dy and partial 16-byte aligned.  partial: temp_bytes of temporary space, at
+// least column_sums_temp_bytes (more of it is used as more, shorter row ranges).
 hipError_t column_sums(const float *dy, bool hilo, int64_t rows, int cols, float *out,
-                       float *partial, int64_t max_splits, hipStream_t s);
+                       float *partial, size_t temp_bytes, hipStream_t s);
 size_t column_sums_temp_bytes(int64_t rows, int cols);
 hipError_t validate_csr(const int32_t *indptr, const int32_t *indices, int64_t n_dst,
                         int64_t nnz, int64_t n_src, uint32_t *err, hipStream_t s);
