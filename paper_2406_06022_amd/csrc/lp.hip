@@ -14,6 +14,10 @@
 // products dU_i * h_src_i for the gradient of r; (5) for shared negatives (joint,
 // in-batch) the negative rows' gradients per column, sum_i G_ik u_i, one add per column;
 // (6) the column sums that give the gradient of r.
+//
+// Large per-edge batches take k_lp_edges and k_lp_rows instead: passes (1), (2) and dU_i in
+// one read of the negatives' rows, then the embedding gradient row by row over the edges
+// sorted by row.
 #include "common.h"
 
 namespace rgcn {
@@ -507,6 +511,454 @@ __global__ __launch_bounds__(kThreads) void k_lp_negatives(int32_t mode, int64_t
     }
 }
 
+// ------------------------------------------------------------------ per-edge negatives
+// The path of large per-edge batches: scores, loss and every gradient with each negative's
+// row read once, and the embedding gradient summed row by row instead of by atomics.
+//
+// k_lp_edges: one group of G lanes per positive holds u_i = h_src_i * r and takes the
+// negatives Q at a time; the score of a row and its share of dU_i come from the same
+// registers.  The derivative of the cross entropy needs the one score; the contrastive
+// loss keeps a running maximum m and normaliser z and rescales dU_i when m grows, so the
+// weights of the earlier negatives stay relative to the current maximum.  Left per
+// positive: the derivative of the positive's score (gpos) and, contrastive, m and
+// 1 / (z B), from which any later pass has the derivative of an edge from its score.
+// Bound by the negatives' rows, 65,536 x 32 at d 512 in bf16 reading 2.2 GB, and by the
+// waves in flight that hide their latency: with the rows unpacked for both uses and every
+// lane working out every exponential it took 191 registers, two waves per SIMD, and 976 us;
+// eight rows per batch at four waves per SIMD take 510 us (two batches of four in flight
+// 850, six waves 690).
+constexpr int kFinalCols = 8;
+constexpr int64_t kEdgesMin = 1 << 20;   // batch x negatives x width
+__device__ __forceinline__ float edge_weight(const LpArgs &a, float s, float m, float inv) {
+    return a.loss == RGCN_LP_CONTRASTIVE ? expf(s - m) * inv : sigmoid_f(s) * inv;
+}
+
+template <bool BF16>
+__device__ __forceinline__ void unpack_chunk(const uint4 w, float *v) {
+    if constexpr (BF16) {
+        v[0] = bf16_lo(w.x); v[1] = bf16_hi(w.x); v[2] = bf16_lo(w.y); v[3] = bf16_hi(w.y);
+        v[4] = bf16_lo(w.z); v[5] = bf16_hi(w.z); v[6] = bf16_lo(w.w); v[7] = bf16_hi(w.w);
+    } else {
+        v[0] = __uint_as_float(w.x); v[1] = __uint_as_float(w.y);
+        v[2] = __uint_as_float(w.z); v[3] = __uint_as_float(w.w);
+    }
+}
+template <bool BF16>
+__device__ __forceinline__ uint4 raw_chunk(const LpArgs &a, int64_t row, int c) {
+    return *(const uint4 *)((const char *)a.emb + (row * a.ld * (BF16 ? 2 : 4)) + (int64_t)c * 16);
+}
+
+// part_loss: one partial loss per workgroup; part_rel: one row of d partial sums of
+// dU_i * h_src_i per workgroup (NULL: no relation gradient); grad = 0: scores and loss only.
+// Waves in flight hide the rows' latency, so registers are kept for them: the relation
+// vector and the destination row are read again (from cache) where they are needed, and the
+// relation gradient is summed in LDS, once per positive.
+template <bool BF16, int CPL>
+__global__ __launch_bounds__(kThreads, CPL == 1 ? 4 : 1) void k_lp_edges(
+    LpArgs a, int G, float *pos, float *S, float *gpos, float2 *mz, float *part_loss,
+    float *part_rel, float *d_emb, int grad) {
+    constexpr int VEC = Row<BF16>::VEC;
+    constexpr int Q = CPL >= 4 ? 2 : 8 / CPL;   // rows in flight per lane
+    constexpr int W = kThreads / 64;
+    __shared__ __attribute__((aligned(16))) float s_du[W][64 * VEC * CPL];
+    __shared__ __attribute__((aligned(16))) float s_rel[W][64 * VEC * CPL];
+    __shared__ float s_loss[kThreads];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lg = lane & (G - 1), g0 = lane - lg;
+    const int64_t groups = (int64_t)gridDim.x * (kThreads / G);
+    const int chunks = a.d / VEC;
+    const bool contrastive = a.loss == RGCN_LP_CONTRASTIVE;
+    const float inv_ce = (float)(1.0 / ((double)a.batch * (double)(1 + a.nn)));
+    // this group's part of the two LDS rows, chunk c at c * VEC
+    float *st = &s_du[wave][g0 * VEC * CPL], *rl = &s_rel[wave][g0 * VEC * CPL];
+#pragma unroll
+    for (int p = 0; p < CPL; ++p)
+#pragma unroll
+        for (int e = 0; e < VEC; e += 4)
+            *(f32x4 *)(rl + (lg + p * G) * VEC + e) = f32x4{0.f, 0.f, 0.f, 0.f};
+    float loss = 0.f;
+    for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / G; i < a.batch; i += groups) {
+        uint4 hs[CPL];
+        float u[CPL][VEC], du[CPL][VEC];
+        const int64_t sr = a.src[i], dr = a.dst[i];
+        int32_t nrow = lg < a.nn ? a.neg[i * a.k + lg] : 0;
+        float sp = 0.f;
+#pragma unroll
+        for (int p = 0; p < CPL; ++p) {
+            const int c = lg + p * G;
+            hs[p] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) u[p][e] = du[p][e] = 0.f;
+            if (c < chunks) {
+                float h[VEC], v[VEC], r[VEC];
+                hs[p] = raw_chunk<BF16>(a, sr, c);
+                load_chunk<BF16>(a, dr, c, v);
+                load_rel<BF16>(a, c, r);
+                unpack_chunk<BF16>(hs[p], h);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    u[p][e] = h[e] * r[e];
+                    sp += u[p][e] * v[e];
+                }
+            }
+        }
+        sp = group_sum(sp, G);
+        // contrastive: z starts with the positive's exp(sp - m); a positive score of +inf or
+        // NaN makes every result of the positive NaN, as exp(sp - m) itself would
+        float m = sp, z = lg != 0 ? 0.f : (sp < INFINITY ? 1.f : sp - sp), l = 0.f;
+        for (int64_t kc = 0; kc < a.nn; kc += G) {
+            // the group's next G negatives, one row index per lane
+            const int kn = a.nn - kc < G ? (int)(a.nn - kc) : G;
+            if (kc > 0) nrow = lg < kn ? a.neg[i * a.k + kc + lg] : 0;
+            float mine = 0.f;   // this lane's negative's score
+            for (int k0 = 0; k0 < kn; k0 += Q) {
+                uint4 w[Q][CPL];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    // past the last negative the first of the batch is read again, unused
+                    const int64_t row = __shfl(nrow, g0 + (k0 + q < kn ? k0 + q : k0), 64);
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        const int c = lg + p * G;
+                        w[q][p] = raw_chunk<BF16>(a, row, c < chunks ? c : 0);
+                    }
+                }
+                float s[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    s[q] = 0.f;
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        float v[VEC];
+                        unpack_chunk<BF16>(w[q][p], v);
+                        // lanes past the row hold u = 0 and must not meet an infinity
+                        if (lg + p * G < chunks)
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) s[q] += u[p][e] * v[e];
+                    }
+                }
+                // the Q sums at once: each of the first log2(Q) exchanges halves the values
+                // a lane carries, and lane lg ends with the score of negative k0 + lg % Q,
+                // whose exponentials it alone works out
+#pragma unroll
+                for (int h = 1; h < Q; h <<= 1) {
+                    const bool up = (lg & h) != 0;
+#pragma unroll
+                    for (int q = 0; q < Q; q += 2 * h) {
+                        const float keep = up ? s[q + h] : s[q], give = up ? s[q] : s[q + h];
+                        s[q] = keep + __shfl_xor(give, h, 64);
+                    }
+                }
+                float sc = s[0];
+                for (int o = Q; o < G; o <<= 1) sc += __shfl_xor(sc, o, 64);
+                const bool okq = k0 + (lg & (Q - 1)) < kn;
+                if ((lg & ~(Q - 1)) == k0) mine = sc;
+                float wt;
+                if (contrastive) {
+                    float mn = okq ? fmaxf(m, sc) : m;
+#pragma unroll
+                    for (int h = 1; h < Q; h <<= 1) mn = fmaxf(mn, __shfl_xor(mn, h, 64));
+                    if (!(mn == m)) {   // rescale what was summed under the old maximum
+                        const float f = expf(m - mn);
+                        z *= f;
+#pragma unroll
+                        for (int p = 0; p < CPL; ++p)
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) du[p][e] *= f;
+                        m = mn;
+                    }
+                    wt = okq ? expf(sc - m) : 0.f;
+                    if (lg < Q) z += wt;
+                } else {
+                    wt = okq ? sigmoid_f(sc) * inv_ce : 0.f;
+                    if (lg < Q && okq) l += softplus_f(sc);
+                }
+                // keep the rows packed between their two uses (unpacked they cost waves)
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p)
+                        asm volatile("" : "+v"(w[q][p].x), "+v"(w[q][p].y), "+v"(w[q][p].z),
+                                          "+v"(w[q][p].w));
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const float wq = __shfl(wt, g0 + q, 64);
+                    if (k0 + q >= kn) continue;   // an absent row adds nothing
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        float v[VEC];
+                        unpack_chunk<BF16>(w[q][p], v);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) du[p][e] += wq * v[e];
+                    }
+                }
+            }
+            if (lg < kn) S[i * a.nn + kc + lg] = mine;
+        }
+        // the normaliser and the loss terms of the lanes that held them
+        float gp, scale = 1.f;
+        if (contrastive) {
+#pragma unroll
+            for (int h = 1; h < Q; h <<= 1) z += __shfl_xor(z, h, 64);
+            z = __shfl(z, g0, 64);
+            scale = 1.f / (z * (float)a.batch);
+            gp = expf(sp - m) * scale - 1.f / (float)a.batch;
+            loss += lg == 0 ? (m + logf(z) - sp) / (float)a.batch : 0.f;
+            if (lg == 0) mz[i] = make_float2(m, scale);
+        } else {
+#pragma unroll
+            for (int h = 1; h < Q; h <<= 1) l += __shfl_xor(l, h, 64);
+            const float wp = (a.loss == RGCN_LP_WEIGHTED_CE && a.pos_weight) ? a.pos_weight[i] : 1.f;
+            gp = wp * (sigmoid_f(sp) - 1.f) * inv_ce;
+            loss += lg == 0 ? (l + wp * softplus_f(-sp)) * inv_ce : 0.f;
+        }
+        if (lg == 0) {
+            pos[i] = sp;
+            gpos[i] = gp;
+        }
+        if (!grad) continue;
+        // dU_i complete; its product with r into the source row, through LDS so that a
+        // group's atomics cover consecutive floats
+#pragma unroll
+        for (int p = 0; p < CPL; ++p) {
+            const int c = lg + p * G;
+            if (c >= chunks) continue;
+            float h[VEC], v[VEC], r[VEC];
+            load_chunk<BF16>(a, dr, c, v);
+            load_rel<BF16>(a, c, r);
+            unpack_chunk<BF16>(hs[p], h);
+#pragma unroll
+            for (int e = 0; e < VEC; e += 4) {
+                f32x4 t, x, *acc = (f32x4 *)(rl + c * VEC + e);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    x[q] = du[p][e + q] * scale + gp * v[e + q];
+                    t[q] = x[q] * r[e + q];
+                    x[q] *= h[e + q];
+                }
+                if (part_rel != nullptr) *acc += x;
+                *(f32x4 *)(st + c * VEC + e) = t;
+            }
+        }
+        if (d_emb != nullptr) {
+            __builtin_amdgcn_wave_barrier();
+            for (int e = lg; e < a.d; e += G) unsafeAtomicAdd(d_emb + sr * a.d + e, st[e]);
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    // the workgroup's partial loss, and its row of the relation gradient's partial sums
+    s_loss[threadIdx.x] = loss;
+    __syncthreads();
+    for (int o = kThreads / 2; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) s_loss[threadIdx.x] += s_loss[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) part_loss[blockIdx.x] = s_loss[0];
+    if (!grad || part_rel == nullptr) return;
+    const float *all = &s_rel[0][0];
+    const int ngrp = kThreads / G, pitch = G * VEC * CPL;
+    for (int e = threadIdx.x; e < a.d; e += kThreads) {
+        float t = 0.f;
+        for (int q = 0; q < ngrp; ++q) t += all[q * pitch + e];
+        part_rel[(int64_t)blockIdx.x * a.d + e] = t;
+    }
+}
+
+// The workgroups' partial losses and relation gradients, each added in a fixed order:
+// workgroup 0 the loss, the others 8 columns of d_rel each with 32 lanes per column.
+__global__ __launch_bounds__(kThreads) void k_lp_edges_final(const float *part_loss,
+                                                             const float *part_rel, int n, int d,
+                                                             float *loss, float *d_rel) {
+    __shared__ float buf[kThreads];
+    float acc = 0.f;
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < n; i += kThreads) acc += part_loss[i];
+        buf[threadIdx.x] = acc;
+        __syncthreads();
+        for (int o = kThreads / 2; o > 0; o >>= 1) {
+            if ((int)threadIdx.x < o) buf[threadIdx.x] += buf[threadIdx.x + o];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = buf[0];
+        return;
+    }
+    const int c = threadIdx.x % kFinalCols, l = threadIdx.x / kFinalCols;
+    const int e = ((int)blockIdx.x - 1) * kFinalCols + c;
+    if (e < d)
+#pragma unroll 8
+        for (int i = l; i < n; i += kThreads / kFinalCols) acc += part_rel[(int64_t)i * d + e];
+    buf[threadIdx.x] = acc;
+    __syncthreads();
+    for (int o = kThreads / 2; o >= kFinalCols; o >>= 1) {
+        if ((int)threadIdx.x < o) buf[threadIdx.x] += buf[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (l == 0 && e < d) d_rel[e] = buf[c];
+}
+
+// The edges by the embedding row whose gradient they add to: edge e < B K is negative
+// e % K of positive e / K (row neg[e]), edge B K + i the positive i (row dst[i]).  A count
+// per row whose atomic also gives each edge its place in the row's segment, the counts'
+// exclusive scan (off), and the placement; the order inside a segment varies from run to
+// run.
+__device__ __forceinline__ int32_t edge_row(const LpArgs &a, int64_t e, int64_t bk) {
+    return e < bk ? a.neg[e] : a.dst[e - bk];
+}
+__global__ __launch_bounds__(kThreads) void k_lp_clear(int32_t *p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kThreads)
+        p[i] = 0;
+}
+__global__ __launch_bounds__(kThreads) void k_lp_count(LpArgs a, int32_t *cnt, int32_t *rank) {
+    const int64_t bk = a.batch * a.nn, n = bk + a.batch;
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < n;
+         e += (int64_t)gridDim.x * kThreads) {
+        const int32_t row = edge_row(a, e, bk);
+        if (row >= 0 && row < a.n_rows) rank[e] = atomicAdd(&cnt[row], 1);
+    }
+}
+__global__ __launch_bounds__(kThreads) void k_lp_place(LpArgs a, const int32_t *off,
+                                                       const int32_t *rank, int32_t *ent) {
+    const int64_t bk = a.batch * a.nn, n = bk + a.batch;
+    for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < n;
+         e += (int64_t)gridDim.x * kThreads) {
+        const int32_t row = edge_row(a, e, bk);
+        if (row >= 0 && row < a.n_rows) ent[off[row] + rank[e]] = (int32_t)e;
+    }
+}
+
+// d_emb[v] += sum over the edges of row v of G_e u_i, a row read and written once.  A
+// group of G lanes (at least kRowStep) takes kRowChunk consecutive edges of the sorted
+// list, extended to the end of the last row that starts in them; a row of more than
+// kRowLong edges is cut at the chunks and its pieces added by atomics, so one popular row
+// does not hold a single group up.  kRowStep edges are resolved at a time, one per lane (edge, row,
+// positive, weight), then their u rows and the gradient rows that end among them are all
+// in flight before any is used.  The rows h_src_i are read again from emb (a batch's source
+// rows stay in the last-level cache) instead of a stored u_i, and r multiplies the finished
+// sum.
+// Bound by the gradient rows' read and write (65,536 x 32 at d 512 in bf16 over 1M rows:
+// 3.6 GB, and 2.2 GB of source rows from cache, 950 us where 1.07 G atomics took 3,500).
+constexpr int kRowChunk = 32, kRowLong = 128, kRowStep = 8;
+template <bool BF16, int CPL>
+__global__ __launch_bounds__(kThreads) void k_lp_rows(LpArgs a, int G, const int32_t *off,
+                                                      const int32_t *ent, const float *S,
+                                                      const float *gpos, const float2 *mz,
+                                                      float *d_emb) {
+    constexpr int VEC = Row<BF16>::VEC;
+    constexpr int U = CPL >= 4 ? 2 : 4;   // edges in flight
+    const int lane = threadIdx.x & 63;
+    const int lg = lane & (G - 1), g0 = lane - lg;
+    const int chunks = a.d / VEC;
+    const int64_t bk = a.batch * a.nn;
+    const int32_t total = off[a.n_rows];
+    const int64_t groups = (int64_t)gridDim.x * (kThreads / G);
+    const bool contrastive = a.loss == RGCN_LP_CONTRASTIVE;
+    const float inv_ce = (float)(1.0 / ((double)a.batch * (double)(1 + a.nn)));
+    const int64_t nchunk = cdiv(total, kRowChunk);
+    for (int64_t ch = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / G; ch < nchunk; ch += groups) {
+        const int32_t p0 = (int32_t)(ch * kRowChunk);
+        const int32_t p1 = p0 + kRowChunk < total ? p0 + kRowChunk : total;
+        const int32_t r0 = edge_row(a, ent[p0], bk), r1 = edge_row(a, ent[p1 - 1], bk);
+        const int32_t b0 = off[r0], e0 = off[r0 + 1], b1 = off[r1], e1 = off[r1 + 1];
+        // a short row that starts before the chunk belongs to the chunk it starts in
+        const int32_t pb = (b0 < p0 && e0 - b0 <= kRowLong) ? e0 : p0;
+        const int32_t pe = (e1 > p1 && e1 - b1 <= kRowLong && b1 >= p0) ? e1 : p1;
+        float acc[CPL][VEC];
+#pragma unroll
+        for (int p = 0; p < CPL; ++p)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[p][e] = 0.f;
+        for (int32_t ps = pb; ps < pe; ps += kRowStep) {
+            const int n = pe - ps < kRowStep ? pe - ps : kRowStep;
+            // lane lg < n: edge ps + lg.  kind 0: inside its row; 1: ends its row or, of a
+            // long row, this chunk's piece, added in place; 2: the same, added by atomics
+            int32_t row = 0, src = 0;
+            float wt = 0.f;
+            int kind = 0;
+            if (lg < n) {
+                const int32_t e = ent[ps + lg];
+                row = edge_row(a, e, bk);
+                const int64_t i = e < bk ? (int64_t)((uint32_t)e / (uint32_t)a.k) : e - bk;
+                src = a.src[i];
+                if (e < bk) {
+                    const float2 q = contrastive ? mz[i] : make_float2(0.f, inv_ce);
+                    wt = edge_weight(a, S[e], q.x, q.y);
+                } else {
+                    wt = gpos[i];
+                }
+                const int32_t rb = off[row], re = off[row + 1];
+                const bool cut = re - rb > kRowLong;
+                if (ps + lg + 1 == re || (cut && ps + lg + 1 == pe)) kind = cut ? 2 : 1;
+            }
+#pragma unroll
+            for (int u0 = 0; u0 < kRowStep; u0 += U) {
+                if (u0 >= n) break;
+                uint4 w[U][CPL];
+                float4 old[U][CPL][VEC / 4];
+                float wu[U];
+                int32_t ru[U];
+                int ku[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int sl = g0 + u0 + q;
+                    const bool ok = u0 + q < n;
+                    wu[q] = __shfl(wt, sl, 64);
+                    ru[q] = __shfl(row, sl, 64);
+                    const int kq = __shfl(kind, sl, 64);
+                    ku[q] = ok ? kq : 0;
+                    const int64_t su = __shfl(src, sl, 64);
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        const int c = lg + p * G;
+                        w[q][p] = ok && c < chunks ? raw_chunk<BF16>(a, su, c)
+                                                   : make_uint4(0u, 0u, 0u, 0u);
+                        if (ku[q] == 1 && c < chunks)
+#pragma unroll
+                            for (int e = 0; e < VEC / 4; ++e)
+                                old[q][p][e] = *(const float4 *)(d_emb + (int64_t)ru[q] * a.d +
+                                                                 c * VEC + 4 * e);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    if (u0 + q >= n) break;
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        const int c = lg + p * G;
+                        float h[VEC];
+                        unpack_chunk<BF16>(w[q][p], h);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) acc[p][e] += wu[q] * h[e];
+                        if (ku[q] == 0 || c >= chunks) continue;
+                        float *o = d_emb + (int64_t)ru[q] * a.d + c * VEC;
+                        float r[VEC];
+                        load_rel<BF16>(a, c, r);
+                        if (ku[q] == 1) {
+#pragma unroll
+                            for (int e = 0; e < VEC / 4; ++e) {
+                                float4 t = old[q][p][e];
+                                t.x += acc[p][4 * e] * r[4 * e];
+                                t.y += acc[p][4 * e + 1] * r[4 * e + 1];
+                                t.z += acc[p][4 * e + 2] * r[4 * e + 2];
+                                t.w += acc[p][4 * e + 3] * r[4 * e + 3];
+                                *(float4 *)(o + 4 * e) = t;
+                            }
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) unsafeAtomicAdd(o + e, acc[p][e] * r[e]);
+                        }
+                    }
+                    if (ku[q] != 0)
+#pragma unroll
+                        for (int p = 0; p < CPL; ++p)
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) acc[p][e] = 0.f;
+                }
+            }
+        }
+    }
+}
+
 int64_t grid_for(int64_t items, int per_wg) {
     int64_t g = cdiv(items, per_wg);
     if (g < 1) g = 1;
@@ -549,6 +1001,87 @@ hipError_t dispatch_finish(const LpArgs &a, const float *gpos, const float *Gm, 
     else if (J <= 32) RGCN_FIN(32);
     else return hipErrorInvalidValue;
 #undef RGCN_FIN
+    return hipGetLastError();
+}
+
+// Space of the per-edge path inside the workspace of the other one: its tables take the
+// place of the stored u and of the products for d_rel (off_U up to off_colsum), which it
+// does not need, so no workspace grows.  ok is false where they do not fit there.
+struct EdgePlan {
+    bool ok;
+    int G, cpl;
+    int64_t grid;
+    size_t cnt, off, scan, rank, ent, mz, loss, rel;
+};
+EdgePlan edge_plan(const LpArgs &a, const LpLayout &L) {
+    EdgePlan e{};
+    const int chunks = a.d / (a.dtype == RGCN_BF16 ? 8 : 4);
+    e.G = kRowStep;
+    while (e.G < chunks && e.G < 64) e.G *= 2;
+    e.cpl = (int)cdiv(chunks, e.G);
+    const int64_t edges = a.batch * a.nn + a.batch;
+    if (edges >= 2147483647 || a.n_rows + 1 >= 2147483647) return e;
+    // four workgroups per CU are resident; each writes a row of partial sums
+    e.grid = cdiv(a.batch, kThreads / e.G);
+    if (e.grid > 1024) e.grid = 1024;
+    auto al = [](size_t x) { return (x + 255) / 256 * 256; };
+    size_t o = L.off_U;
+    e.cnt = o;  o += al((size_t)(a.n_rows + 1) * 4);
+    e.off = o;  o += al((size_t)(a.n_rows + 1) * 4);
+    e.scan = o; o += al(scan_temp_bytes(a.n_rows + 1));
+    e.rank = o; o += al((size_t)edges * 4);
+    e.ent = o;  o += al((size_t)edges * 4);
+    e.mz = o;   o += al((size_t)a.batch * 8);
+    e.loss = o; o += al((size_t)e.grid * 4);
+    e.rel = o;  o += al((size_t)e.grid * a.d * 4);
+    e.ok = o <= L.off_colsum;
+    return e;
+}
+
+template <bool BF16, int CPL>
+hipError_t run_edges(const LpArgs &a, const EdgePlan &e, char *ws, float *pos, float *S,
+                     float *gpos, float *d_emb, float *d_rel, hipStream_t s) {
+    const int32_t *off = (const int32_t *)(ws + e.off), *ent = (const int32_t *)(ws + e.ent);
+    float2 *mz = (float2 *)(ws + e.mz);
+    hipLaunchKernelGGL((k_lp_edges<BF16, CPL>), dim3((unsigned)e.grid), dim3(kThreads), 0, s, a,
+                       e.G, pos, S, gpos, mz, (float *)(ws + e.loss),
+                       d_rel ? (float *)(ws + e.rel) : nullptr, d_emb, d_emb || d_rel ? 1 : 0);
+    RGCN_HIP_TRY(hipGetLastError());
+    if (!d_emb) return hipSuccess;
+    int64_t wgs = cdiv(cdiv(a.batch * (a.nn + 1), kRowChunk), kThreads / e.G);
+    if (wgs > 4096) wgs = 4096;
+    hipLaunchKernelGGL((k_lp_rows<BF16, CPL>), dim3((unsigned)wgs), dim3(kThreads), 0, s, a, e.G,
+                       off, ent, S, gpos, mz, d_emb);
+    return hipGetLastError();
+}
+
+hipError_t lp_edges(const LpArgs &a, const EdgePlan &e, char *ws, float *loss, float *pos,
+                    float *S, float *gpos, float *d_emb, float *d_rel, hipStream_t s) {
+    int32_t *cnt = (int32_t *)(ws + e.cnt), *off = (int32_t *)(ws + e.off);
+    const int64_t edges = a.batch * a.nn + a.batch;
+    if (d_emb) {
+        const dim3 grid((unsigned)grid_for(edges, kThreads));
+        hipLaunchKernelGGL(k_lp_clear, dim3((unsigned)grid_for(a.n_rows + 1, kThreads)),
+                           dim3(kThreads), 0, s, cnt, a.n_rows + 1);
+        RGCN_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(k_lp_count, grid, dim3(kThreads), 0, s, a, cnt,
+                           (int32_t *)(ws + e.rank));
+        RGCN_HIP_TRY(hipGetLastError());
+        RGCN_HIP_TRY(exclusive_scan_i32(cnt, off, a.n_rows + 1, ws + e.scan, s));
+        hipLaunchKernelGGL(k_lp_place, grid, dim3(kThreads), 0, s, a, off,
+                           (const int32_t *)(ws + e.rank), (int32_t *)(ws + e.ent));
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+#define RGCN_EDGES(B_, C_) RGCN_HIP_TRY((run_edges<B_, C_>(a, e, ws, pos, S, gpos, d_emb, d_rel, s)))
+    const bool bf = a.dtype == RGCN_BF16;
+    if (e.cpl == 1) { if (bf) RGCN_EDGES(true, 1); else RGCN_EDGES(false, 1); }
+    else if (e.cpl == 2) { if (bf) RGCN_EDGES(true, 2); else RGCN_EDGES(false, 2); }
+    else if (e.cpl <= 4) { if (bf) RGCN_EDGES(true, 4); else RGCN_EDGES(false, 4); }
+    else return hipErrorInvalidValue;
+#undef RGCN_EDGES
+    hipLaunchKernelGGL(k_lp_edges_final, dim3((unsigned)(1 + (d_rel ? cdiv(a.d, kFinalCols) : 0))),
+                       dim3(kThreads), 0, s, (const float *)(ws + e.loss),
+                       (const float *)(ws + e.rel), (int)e.grid, a.d, loss, d_rel);
     return hipGetLastError();
 }
 
@@ -623,6 +1156,16 @@ hipError_t lp_loss(const LpArgs &a, const LpLayout &L, char *ws, float *loss, fl
         RGCN_HIP_TRY(fill_words(loss, &zero, 4, s));
         if (d_rel) RGCN_HIP_TRY(column_sums(nullptr, false, 0, a.d, d_rel, nullptr, 0, s));
         return hipSuccess;
+    }
+    // Per edge: the row-sorted path, from a million row elements on.  Below, its three more
+    // launches cost more than the atomics they replace (measured, us, atomics / sorted:
+    // 512 x 1 x 64 30 / 44, 300 x 10 x 128 36 / 44, 2,000 x 1 x 256 40 / 46; 128 x 32 x 256
+    // 82 / 50, 16,000 x 1 x 512 254 / 136, 65,536 x 32 x 512 4,760 / 1,880).  It adds whole
+    // 16-byte pieces to d_emb, so a gradient at another alignment keeps the atomics.
+    if (!dense) {
+        const EdgePlan e = edge_plan(a, L);
+        if (e.ok && a.batch * a.nn * a.d >= kEdgesMin && ((uintptr_t)d_emb & 15u) == 0)
+            return lp_edges(a, e, ws, loss, pos, S, gpos, d_emb, d_rel, s);
     }
     // (1) scores: u_i and the positives; per edge also the negatives
     RGCN_HIP_TRY(bf ? dispatch_scores<true>(a, pos, S, U, dense ? 0 : 1, s)

@@ -1,0 +1,68 @@
+"""The row-sorted per-edge decoder (batches of at least 2^20 row elements) at its edges:
+widths that fill one, two and four chunks per lane and leave lanes over, negatives that
+leave partial batches, rows popular enough to be cut into pieces, losses whose running
+maximum moves; against the oracle within the bounds of test_gpu_lp.  And the forms around
+it: a gradient buffer at another alignment, scores only, relation gradient only."""
+import pytest
+import torch
+
+from paper_2406_06022_amd import rgcn
+from test_gpu_lp import TOL, _case, _check, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("dtype,d,n,B,k,hot,distmult", [
+    ("bf16", 512, 900, 257, 9, 0, True),     # 64 chunks: a wave per positive
+    ("f32", 260, 700, 130, 33, 0, True),     # 65 chunks: two per lane, most lanes idle twice
+    ("bf16", 1032, 300, 70, 65, 0, False),   # 129 chunks over four per lane, K past a wave
+    ("f32", 1024, 300, 129, 8, 0, True),
+    ("bf16", 2048, 200, 67, 15, 0, True),
+    ("f32", 40, 4000, 3001, 11, 0, True),    # 10 chunks in groups of 16
+    ("bf16", 64, 50, 2001, 17, 3, True),     # 8 lanes per positive; three rows take most edges
+    ("bf16", 128, 2, 1100, 8, 1, False),     # a row with every negative
+])
+def test_sorted_edges(dtype, d, n, B, k, hot, distmult, kind):
+    assert B * k * d >= 1 << 20
+    emb, rel, src, dst, neg, w = _case(d + B + k + kind, dtype, n, d, B, k, 0)
+    if hot:
+        neg = torch.where(torch.rand(neg.numel()) < 0.9, neg % hot, neg).to(torch.int32)
+    rel = rel if distmult else None
+    print(f"case lp edges loss={kind} {dtype} d={d} B={B} k={k} hot={hot}", flush=True)
+    got = _run(emb, rel, 0, kind, src, dst, k, neg, w)
+    _check(got, emb, rel, 0, kind, src, dst, k, neg, w)
+
+
+def _call(emb, rel, src, dst, neg, k, **out):
+    b = rgcn.lp_batch(emb, rel, 0, rgcn.RGCN_LP_CE, src, dst, k, neg)
+    loss = torch.full((1,), float("nan"), device="cuda")
+    rgcn.rgcn_lp_loss(b, loss, **out)
+    torch.cuda.synchronize()
+    return loss
+
+
+def test_forms_around_the_sorted_path():
+    n, d, B, k = 600, 512, 129, 17
+    emb, rel, src, dst, neg, _ = _case(11, "bf16", n, d, B, k, 0)
+    emb, rel, src, dst, neg = (x.cuda() for x in (emb, rel, src, dst, neg))
+    start = torch.randn((n, d), device="cuda")
+    whole, g_rel = start.clone(), torch.empty(d, device="cuda")
+    want = _call(emb, rel, src, dst, neg, k, d_emb=whole, d_rel=g_rel)
+    # a gradient buffer 4 bytes off: the atomics path, the same sums
+    buf = torch.zeros(n * d + 1, device="cuda")
+    off = buf[1:].view(n, d)
+    off.copy_(start)
+    g2 = torch.empty(d, device="cuda")
+    got = _call(emb, rel, src, dst, neg, k, d_emb=off, d_rel=g2)
+    scale = (whole - start).double().square().mean().sqrt()
+    assert (off - whole).abs().max() <= 4 * TOL * (scale + start.abs().max())
+    assert (g2 - g_rel).abs().max() <= 4 * TOL * g_rel.abs().max()
+    assert abs(float(got - want)) <= TOL * abs(float(want))
+    # the relation gradient alone, the scores alone
+    g3 = torch.empty(d, device="cuda")
+    assert torch.equal(_call(emb, rel, src, dst, neg, k, d_rel=g3), want)
+    assert torch.equal(g3, g_rel)
+    neg_s = torch.full((B, k), float("nan"), device="cuda")
+    assert torch.equal(_call(emb, rel, src, dst, neg, k, neg_score=neg_s), want)
+    assert bool(torch.isfinite(neg_s).all())
