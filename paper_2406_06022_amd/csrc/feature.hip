@@ -5,21 +5,33 @@
 //
 // One group of G lanes per node (G = 16-byte chunks per row, rounded up to a power of
 // two, at least 8, at least the number of relations, at most 64; CPL chunks per lane
-// beyond 64 chunks).  A persistent grid whose groups claim runs of 16 nodes from a
-// counter, so a node of very high degree delays only the group that holds it.  A node's
-// in-edges over all relations form one list: the offsets of every relation are loaded at
-// once (the next node's while this one's rows are in flight), the group loads G ids of the
-// list at a time, and every lane keeps up to 16 row chunks in flight before adding them in
+// beyond 64 chunks).  A persistent grid whose groups take a run of up to 16 nodes each and
+// claim further ones from a counter.  A node of more than kHeavy in-edges is set aside and
+// summed by its whole workgroup once the runs are gone: alone, a group takes a round trip
+// for every batch of rows, so the heaviest nodes of a power-law graph (20,000 in-edges among
+// 4M nodes) set the time.  A node's in-edges over all relations form one list: the offsets
+// of every relation are loaded at once (the next node's while this one's rows are in
+// flight), the group loads G ids of the list at a time (the next G while these ones' rows
+// are in flight), and every lane keeps up to 8 row chunks in flight before adding them in
 // fp32 with compensation.  The mean is written in the table dtype (bf16 rounded to
 // nearest even).
+//
+// HBM-bound: 4M nodes with 60M in-edges of 256-byte rows move 15.8 GB, 3.1 ms at the rate
+// of a large copy.  5,300 us without the heavy nodes' lists, ids loaded between the rows and
+// 16 rows per lane at three waves per SIMD; 3,260 us so (16 rows at four waves 3,490, 4 rows
+// 3,440, six waves 3,940; heavy from 256 in-edges 3,320, from 512 3,500).  Graphs of 20,000 to
+// 300,000 nodes 355 -> 32 us and 2,160 -> 745 us.
 #include "common.h"
 
 namespace rgcn {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kNodeRun = 16;   // nodes claimed at a time
+constexpr int kNodeRun = 16;   // most nodes claimed at a time
+// in-edges from which a node is left to the workgroup, and how many such nodes a workgroup
+// keeps (further ones are summed by the group that meets them)
+constexpr int kHeavy = 128;
+constexpr int kHeavyCap = 64;
 constexpr int kMinGroup = 8;
 
 __host__ __device__ inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -55,21 +67,25 @@ __device__ __forceinline__ void add_chunk(float *acc, float *comp, const uint4 w
 // entry e0 + e (its relation found from the offsets), and every lane then loads its
 // chunk(s) of U of the batch's rows at a time, all U loads in flight before any is added.
 // The next node's offsets are requested before the current node's rows.
-template <bool BF16, int CPL>
-__global__ __launch_bounds__(kThreads) void k_feature_mean(FeatArgs a, int G, uint32_t *claims,
+template <bool BF16, int CPL, int NT>
+__global__ __launch_bounds__(NT, CPL == 1 ? 4 : 1) void k_feature_mean(FeatArgs a, int G, int node_run, uint32_t *claims,
                                                            uint32_t *err) {
     constexpr int VEC = BF16 ? 8 : 4;
-    constexpr int U = 16 / CPL;                  // rows in flight per lane
+    constexpr int U = 8 / CPL;                  // rows in flight per lane
     constexpr int ES = BF16 ? 2 : 4;
     __shared__ FeatRel s_rel[kMaxRels];
-    for (int i = threadIdx.x; i < a.nrel; i += kThreads) s_rel[i] = a.rel[i];
+    __shared__ int64_t s_heavy[kHeavyCap];
+    __shared__ int s_nheavy;
+    __shared__ float s_part[(NT / 64)][64 * VEC * CPL];
+    for (int i = threadIdx.x; i < a.nrel; i += NT) s_rel[i] = a.rel[i];
+    if (threadIdx.x == 0) s_nheavy = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int lg = lane & (G - 1);
     const int g0 = lane - lg;
     const int chunks = a.d / VEC;
     const int nrel = a.nrel;
-    const int64_t runs = cdiv(a.num_nodes, kNodeRun);
+    const int64_t runs = cdiv(a.num_nodes, node_run);
     // this lane's relation (lg < nrel): begin and end of node v's in-edges
     auto load_range = [&](int64_t v, int64_t &b, int64_t &e) {
         b = e = 0;
@@ -78,132 +94,210 @@ __global__ __launch_bounds__(kThreads) void k_feature_mean(FeatArgs a, int G, ui
             e = s_rel[lg].indptr[v + 1];
         }
     };
-    while (true) {
-        uint32_t run = 0;
-        if (lg == 0) run = atomicAdd(claims, 1u);
-        run = __shfl(run, g0, 64);
-        if ((int64_t)run >= runs) break;
-        const int64_t vb = (int64_t)run * kNodeRun;
-        const int64_t v1 = vb + kNodeRun < a.num_nodes ? vb + kNodeRun : a.num_nodes;
+    // flattened list of a node's in-edges: relation r covers [start_r, start_r + deg_r)
+    auto flatten = [&](int64_t rb, int64_t re, int64_t &deg, int64_t &start) -> int64_t {
+        deg = re - rb;
+        int64_t incl = deg;
+        for (int off = 1; off < G; off <<= 1) {
+            const int64_t o = shfl64(incl, g0 + (lg >= off ? lg - off : lg));
+            if (lg >= off) incl += o;
+        }
+        start = incl - deg;
+        return shfl64(incl, g0 + G - 1);
+    };
+    float acc[CPL][VEC], comp[CPL][VEC];
+    // acc / comp = the compensated sum of list entries [b0, b0 + G), [b0 + step, ..) ..
+    // below total; the ids of the next G entries are loaded while the rows of these are in
+    // flight
+    auto sum_rows = [&](int64_t rb, int64_t deg, int64_t start, int64_t total, int64_t b0,
+                        int64_t step) {
+#pragma unroll
+        for (int p = 0; p < CPL; ++p)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[p][e] = comp[p][e] = 0.f;
+        // lane lg: entry f = e0 + lg -> its relation (last r with start_r <= f and
+        // deg_r > 0) and id
+        auto resolve = [&](int64_t e0, int &rel, int64_t &id) {
+            const int64_t f = e0 + lg;
+            rel = 0;
+            int64_t pos = 0;
+            for (int r = 0; r < nrel; ++r) {
+                const int64_t sr = shfl64(start, g0 + r);
+                const int64_t dr = shfl64(deg, g0 + r);
+                const int64_t br = shfl64(rb, g0 + r);
+                if (f >= sr && f < sr + dr) {
+                    rel = r;
+                    pos = br + (f - sr);
+                }
+            }
+            id = -1;
+            if (f < total) {
+                id = s_rel[rel].indices[pos];
+                if (id < 0 || id >= s_rel[rel].rows) {
+                    atomicOr(err, 1u);
+                    id = -1;
+                }
+            }
+        };
+        int rel = 0, nrl = 0;
+        int64_t id = -1, nid = -1;
+        if (b0 < total) resolve(b0, rel, id);
+        for (int64_t e0 = b0; e0 < total; e0 += step) {
+            const int cnt = total - e0 < G ? (int)(total - e0) : G;
+            for (int u0 = 0; u0 < cnt; u0 += U) {
+                uint4 w[U][CPL];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int src = g0 + ((u0 + u) & (G - 1));
+                    const int64_t idu = shfl64(id, src);
+                    const int relu = __shfl(rel, src, 64);
+                    const bool ok = u0 + u < cnt && idu >= 0;
+                    const FeatRel &R = s_rel[relu];
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) {
+                        const int c = lg + p * G;
+                        if (ok && c < chunks)
+                            w[u][p] = *(const uint4 *)((const char *)R.feat +
+                                                       idu * R.ld * ES + (int64_t)c * 16);
+                        else
+                            w[u][p] = make_uint4(0u, 0u, 0u, 0u);
+                    }
+                }
+                if (u0 == 0 && e0 + step < total) resolve(e0 + step, nrl, nid);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int p = 0; p < CPL; ++p) add_chunk<BF16>(acc[p], comp[p], w[u][p]);
+            }
+            rel = nrl;
+            id = nid;
+        }
+    };
+    // the mean of node v from its sum in acc, by the lanes of one group
+    auto store = [&](int64_t v, int64_t total) {
+        const float fc = (float)total;
+        const float rc = total > 0 ? 1.f / fc : 0.f;
+#pragma unroll
+        for (int p = 0; p < CPL; ++p) {
+            const int c = lg + p * G;
+            if (c >= chunks) continue;
+            float q[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                // one correction step from the exact remainder keeps fp32 output
+                // within an ulp of the quotient
+                const float sum = acc[p][e] - comp[p][e];
+                const float q0 = sum * rc;
+                q[e] = total > 0 ? __builtin_fmaf(__builtin_fmaf(-q0, fc, sum), rc, q0) : 0.f;
+            }
+            char *o = (char *)a.out + (v * a.out_ld + (int64_t)c * VEC) * ES;
+            if constexpr (BF16) {
+                *(uint4 *)o = make_uint4(pack_bf16x2(q[0], q[1]), pack_bf16x2(q[2], q[3]),
+                                         pack_bf16x2(q[4], q[5]), pack_bf16x2(q[6], q[7]));
+            } else {
+                *(uint4 *)o = make_uint4(__float_as_uint(q[0]), __float_as_uint(q[1]),
+                                         __float_as_uint(q[2]), __float_as_uint(q[3]));
+            }
+        }
+    };
+    // run gid first, then claimed ones (none where every run has a group already)
+    const int64_t ngroups = (int64_t)gridDim.x * (NT / G);
+    int64_t run = ((int64_t)blockIdx.x * NT + threadIdx.x) / G;
+    while (run < runs) {
+        const int64_t vb = run * node_run;
+        const int64_t v1 = vb + node_run < a.num_nodes ? vb + node_run : a.num_nodes;
         int64_t nb, ne;
         load_range(vb, nb, ne);
         for (int64_t v = vb; v < v1; ++v) {
             const int64_t rb = nb, re = ne;
             load_range(v + 1 < v1 ? v + 1 : a.num_nodes, nb, ne);   // next node, in flight
-            // flattened list: relation r covers [start_r, start_r + deg_r)
-            const int64_t deg = re - rb;
-            int64_t incl = deg;
-            for (int off = 1; off < G; off <<= 1) {
-                const int64_t o = shfl64(incl, g0 + (lg >= off ? lg - off : lg));
-                if (lg >= off) incl += o;
+            int64_t deg, start;
+            const int64_t total = flatten(rb, re, deg, start);
+            if (total > kHeavy) {
+                int slot = 0;
+                if (lg == 0) slot = atomicAdd(&s_nheavy, 1);
+                slot = __shfl(slot, g0, 64);
+                if (slot < kHeavyCap) {
+                    if (lg == 0) s_heavy[slot] = v;
+                    continue;
+                }
             }
-            const int64_t total = shfl64(incl, g0 + G - 1);
-            const int64_t start = incl - deg;
-            float acc[CPL][VEC], comp[CPL][VEC];
+            sum_rows(rb, deg, start, total, 0, G);
+            store(v, total);
+        }
+        if (runs <= ngroups) break;
+        uint32_t claimed = 0;
+        if (lg == 0) claimed = atomicAdd(claims, 1u);
+        run = ngroups + (int64_t)(uint32_t)__shfl((int)claimed, g0, 64);
+    }
+    // the nodes set aside: every group of the workgroup sums a share of the list, the groups
+    // of a wave meet through shuffles and the waves in LDS, added with compensation in a
+    // fixed order
+    __syncthreads();
+    const int nheavy = s_nheavy < kHeavyCap ? s_nheavy : kHeavyCap;
+    const int ngrp = NT / G, grp = threadIdx.x / G;
+    const int wave = threadIdx.x >> 6;
+    for (int q = 0; q < nheavy; ++q) {
+        const int64_t v = s_heavy[q];
+        int64_t rb, re, deg, start;
+        load_range(v, rb, re);
+        const int64_t total = flatten(rb, re, deg, start);
+        sum_rows(rb, deg, start, total, (int64_t)grp * G, (int64_t)ngrp * G);
+#pragma unroll
+        for (int p = 0; p < CPL; ++p)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                float s = acc[p][e] - comp[p][e], c = 0.f;
+                for (int o = G; o < 64; o <<= 1) {
+                    const float x = __shfl_xor(s, o, 64), xc = __shfl_xor(c, o, 64);
+                    kahan_add(s, c, x);
+                    c += xc;
+                }
+                if (lane < G) s_part[wave][(lg + p * G) * VEC + e] = s - c;
+            }
+        __syncthreads();
+        if (wave == 0 && lane < G) {
 #pragma unroll
             for (int p = 0; p < CPL; ++p)
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) acc[p][e] = comp[p][e] = 0.f;
-            for (int64_t e0 = 0; e0 < total; e0 += G) {
-                // lane lg: entry f = e0 + lg -> its relation (last r with start_r <= f and
-                // deg_r > 0) and id
-                const int64_t f = e0 + lg;
-                int rel = 0;
-                int64_t pos = 0;
-                for (int r = 0; r < nrel; ++r) {
-                    const int64_t sr = shfl64(start, g0 + r);
-                    const int64_t dr = shfl64(deg, g0 + r);
-                    const int64_t br = shfl64(rb, g0 + r);
-                    if (f >= sr && f < sr + dr) {
-                        rel = r;
-                        pos = br + (f - sr);
-                    }
-                }
-                int64_t id = -1;
-                if (f < total) {
-                    id = s_rel[rel].indices[pos];
-                    if (id < 0 || id >= s_rel[rel].rows) {
-                        atomicOr(err, 1u);
-                        id = -1;
-                    }
-                }
-                const int cnt = total - e0 < G ? (int)(total - e0) : G;
-                for (int u0 = 0; u0 < cnt; u0 += U) {
-                    uint4 w[U][CPL];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int src = g0 + ((u0 + u) & (G - 1));
-                        const int64_t idu = shfl64(id, src);
-                        const int relu = __shfl(rel, src, 64);
-                        const bool ok = u0 + u < cnt && idu >= 0;
-                        const FeatRel &R = s_rel[relu];
-#pragma unroll
-                        for (int p = 0; p < CPL; ++p) {
-                            const int c = lg + p * G;
-                            if (ok && c < chunks)
-                                w[u][p] = *(const uint4 *)((const char *)R.feat +
-                                                           idu * R.ld * ES + (int64_t)c * 16);
-                            else
-                                w[u][p] = make_uint4(0u, 0u, 0u, 0u);
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u)
-#pragma unroll
-                        for (int p = 0; p < CPL; ++p) add_chunk<BF16>(acc[p], comp[p], w[u][p]);
-                }
-            }
-            const float fc = (float)total;
-            const float rc = total > 0 ? 1.f / fc : 0.f;
-#pragma unroll
-            for (int p = 0; p < CPL; ++p) {
-                const int c = lg + p * G;
-                if (c >= chunks) continue;
-                float q[VEC];
-#pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    // one correction step from the exact remainder keeps fp32 output
-                    // within an ulp of the quotient
-                    const float sum = acc[p][e] - comp[p][e];
-                    const float q0 = sum * rc;
-                    q[e] = total > 0 ? __builtin_fmaf(__builtin_fmaf(-q0, fc, sum), rc, q0) : 0.f;
+                    acc[p][e] = comp[p][e] = 0.f;
+                    for (int w = 0; w < (NT / 64); ++w)
+                        kahan_add(acc[p][e], comp[p][e], s_part[w][(lg + p * G) * VEC + e]);
                 }
-                char *o = (char *)a.out + (v * a.out_ld + (int64_t)c * VEC) * ES;
-                if constexpr (BF16) {
-                    *(uint4 *)o = make_uint4(pack_bf16x2(q[0], q[1]), pack_bf16x2(q[2], q[3]),
-                                             pack_bf16x2(q[4], q[5]), pack_bf16x2(q[6], q[7]));
-                } else {
-                    *(uint4 *)o = make_uint4(__float_as_uint(q[0]), __float_as_uint(q[1]),
-                                             __float_as_uint(q[2]), __float_as_uint(q[3]));
-                }
-            }
+            store(v, total);
         }
+        __syncthreads();
     }
 }
 
 template <class K>
-int64_t resident(K kernel) {
+int64_t resident(K kernel, int threads) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0) != hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
-    }
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        cus = 256;
     return (int64_t)per_cu * cus;
 }
 
 template <bool B, int C>
 hipError_t launch(const FeatArgs &a, int G, uint32_t *claims, uint32_t *err, hipStream_t s) {
-    const int64_t groups_needed = cdiv(a.num_nodes, kNodeRun);
-    int64_t wgs = cdiv(groups_needed, kThreads / G);
-    const int64_t cap = resident(k_feature_mean<B, C>);
+    // one chunk per lane: large workgroups, so that a heavy node has many groups to share it
+    constexpr int NT = C == 1 ? 512 : 256;
+    const int64_t cap = resident(k_feature_mean<B, C, NT>, NT);
+    // runs of 16 nodes, fewer where that would leave resident groups without one
+    int64_t run = a.num_nodes / (cap * (NT / G));
+    run = run < 1 ? 1 : (run > kNodeRun ? kNodeRun : run);
+    int64_t wgs = cdiv(cdiv(a.num_nodes, run), NT / G);
     if (wgs > cap) wgs = cap;
     if (wgs < 1) wgs = 1;
-    hipLaunchKernelGGL((k_feature_mean<B, C>), dim3((unsigned)wgs), dim3(kThreads), 0, s, a, G,
-                       claims, err);
+    hipLaunchKernelGGL((k_feature_mean<B, C, NT>), dim3((unsigned)wgs), dim3(NT), 0, s, a, G,
+                       (int)run, claims, err);
     return hipGetLastError();
 }
 
