@@ -1252,9 +1252,10 @@ hipError_t launch_flat_k(const SegDesc *desc, const int32_t *cs, int64_t nc_max,
     int64_t wgs = cdiv(cdiv(nc_max, claim), groups_per_wg);
     if (wgs > cap) wgs = cap;
     if (wgs < 1) wgs = 1;
-    // the shared run counter starts past the runs the groups take first
+    // the shared run counter starts past the runs the groups take first; with no more runs
+    // than groups nobody reads it
     const uint32_t first = (uint32_t)(wgs * groups_per_wg);
-    RGCN_HIP_TRY(fill_words(claims, &first, 4, s));
+    if (cdiv(nc_max, claim) > (int64_t)first) RGCN_HIP_TRY(fill_words(claims, &first, 4, s));
     hipLaunchKernelGGL((k_gather_flat<B, G, C, U, FULL>), dim3((unsigned)wgs), dim3(kThreads), 0,
                        s, desc, cs, nc_max, slots_dev, nslots, tabs, ws_base, chunks, claims,
                        (int)claim);

@@ -450,19 +450,6 @@ rgcn_status rgcn_block_plan(const rgcn_block *block, const rgcn_params *params,
     if (parts == 0) parts = RGCN_PLAN_FORWARD | RGCN_PLAN_BACKWARD;
     // flag word 0 belongs to the forward schedule, words 1 + t to the backward ones
     uint32_t *sched_flag = (uint32_t *)(ws + L.off_flags);
-    const uint32_t zeros[1 + kMaxTypes] = {};
-    if (parts & RGCN_PLAN_FORWARD) {
-        if (L.nslots > 0)
-            TRY_HIP(fill_words(ws + L.off_slots, L.slots, sizeof(FwdSlot) * L.nslots, stream),
-                    "slot table");
-        TRY_HIP(fill_words(sched_flag, zeros, sizeof(uint32_t), stream), "schedule flags");
-    }
-    if (parts & RGCN_PLAN_BACKWARD) {
-        TRY_HIP(fill_words(sched_flag + 1, zeros, sizeof(uint32_t) * kMaxTypes, stream),
-                "schedule flags");
-        TRY_HIP(fill_words(sched_flag + kPieceCountWord, zeros, sizeof(uint32_t) * kMaxTypes,
-                           stream), "piece counters");
-    }
     if (parts & RGCN_PLAN_FORWARD) {
         int64_t moff[kMaxTypes], mld[kMaxTypes];
         for (int t = 0; t < kMaxTypes; ++t) {
@@ -471,46 +458,51 @@ rgcn_status rgcn_block_plan(const rgcn_block *block, const rgcn_params *params,
         }
         // segment weights sit in the plan scratch after the chunk pass's own temporaries
         int32_t *weight = (int32_t *)(scratch + fwd_chunks_temp_bytes(L.n_seg));
-        TRY_HIP(fwd_plan(L.slots, L.nslots, L.n_seg, (int32_t *)(ws + L.off_fwd_order), moff, mld,
-                         L.es, (SegDesc *)(ws + L.off_fwd_desc), weight, sched_flag,
-                         keep_order, scratch, stream), "forward schedule");
-        TRY_HIP(fwd_chunks(weight, L.n_seg, L.nc_max, (int32_t *)(ws + L.off_fwd_chunks), scratch,
-                           stream), "forward chunks");
+        TRY_HIP(fwd_plan(L.slots, L.nslots, L.n_seg, (FwdSlot *)(ws + L.off_slots),
+                         (int32_t *)(ws + L.off_fwd_order), moff, mld, L.es,
+                         (SegDesc *)(ws + L.off_fwd_desc), weight, sched_flag, keep_order, L.nc_max,
+                         (int32_t *)(ws + L.off_fwd_chunks), scratch, stream), "forward schedule");
     }
     if (!(parts & RGCN_PLAN_BACKWARD)) return RGCN_OK;
-    if (L.key_range > 0) {
-        CscRels cr{};
-        int64_t rows = 0;
-        for (int r = 0; r < L.R; ++r) {
-            if (L.koff[r] < 0) continue;
-            const rgcn_relation &rel = block->rels[r];
-            cr.row_base[cr.count] = rows;
-            cr.indptr[cr.count] = rel.indptr;
-            cr.indices[cr.count] = rel.indices;
-            cr.koff[cr.count] = L.koff[r];
-            cr.e0[cr.count] = L.e0[r];
-            ++cr.count;
-            rows += block->n_dst[rel.dst_type];
-        }
-        TRY_HIP(csc_build_all(cr, rows, L.csc_nnz, L.key_range, (int32_t *)(ws + L.off_ip),
-                              (int32_t *)(ws + L.off_csd), scratch, stream), "transpose");
+    CscRels cr{};
+    int64_t rows = 0, max_nnz = 0;
+    for (int r = 0; r < L.R; ++r) {
+        if (L.koff[r] < 0) continue;
+        const rgcn_relation &rel = block->rels[r];
+        cr.row_base[cr.count] = rows;
+        cr.indptr[cr.count] = rel.indptr;
+        cr.indices[cr.count] = rel.indices;
+        cr.koff[cr.count] = L.koff[r];
+        cr.e0[cr.count] = L.e0[r];
+        ++cr.count;
+        rows += block->n_dst[rel.dst_type];
+        if (rel.nnz > max_nnz) max_nnz = rel.nnz;
     }
+    BwdType types[kMaxTypes];
+    const int32_t *type_rels[kMaxRels];
+    int ntypes = 0, nr = 0;
     for (int t = 0; t < L.T; ++t) {
         if (!(L.grad_mask >> t & 1u)) continue;
-        BwdKeyRels kr{};
+        BwdType &b = types[ntypes++];
+        b = BwdType{};
+        b.n = block->n_src[t];
+        b.order = (int32_t *)(ws + L.off_bwd_order) + L.bwd_base[t];
+        b.flag = sched_flag + 1 + t;
+        b.rel0 = nr;
         for (int r = 0; r < L.R; ++r)
             if (block->rels[r].src_type == t)
-                kr.csc_indptr[kr.count++] = (const int32_t *)(ws + L.off_csc_indptr[r]);
-        SplitRows sp;
-        sp.np = (int32_t *)(ws + L.off_split_np) + L.bwd_base[t];
-        sp.base = (int32_t *)(ws + L.off_split_base) + L.bwd_base[t];
-        sp.pieces = (int2 *)(ws + L.off_pieces) + L.piece_at[t];
-        sp.count = sched_flag + kPieceCountWord + t;
-        sp.cap = L.piece_cap[t];
-        TRY_HIP(bwd_schedule(kr, block->n_src[t], (int32_t *)(ws + L.off_bwd_order) + L.bwd_base[t],
-                             scratch, sched_flag + 1 + t, keep_order, sp, stream),
-                "backward schedule");
+                type_rels[nr++] = (const int32_t *)(ws + L.off_csc_indptr[r]);
+        b.nrel = nr - b.rel0;
+        b.split.np = (int32_t *)(ws + L.off_split_np) + L.bwd_base[t];
+        b.split.base = (int32_t *)(ws + L.off_split_base) + L.bwd_base[t];
+        b.split.pieces = (int2 *)(ws + L.off_pieces) + L.piece_at[t];
+        b.split.count = sched_flag + kPieceCountWord + t;
+        b.split.cap = L.piece_cap[t];
     }
+    TRY_HIP(bwd_plan(cr, rows, L.csc_nnz, max_nnz, L.key_range, (int32_t *)(ws + L.off_ip),
+                     (int32_t *)(ws + L.off_csd), ntypes, types, type_rels, sched_flag + 1,
+                     sched_flag + kPieceCountWord, keep_order, scratch, stream),
+            "backward schedule");
     return RGCN_OK;
 }
 

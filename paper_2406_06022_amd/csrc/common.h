@@ -140,24 +140,22 @@ size_t scan_temp_bytes(int64_t n);
 hipError_t exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, void *temp,
                               hipStream_t s);
 size_t bucket_sort_temp_bytes(int64_t n, int nbuckets);
-// Forward schedule and segment descriptors in schedule order; mcat_off[t]: byte offset of
-// Mcat_t in the workspace, mcat_ld[t]: its row length in elements, es: element size.
-// weight[p] = balancing weight of segment p in the flattened forward stream: the rows it
-// moves, max(deg, 1) entries read plus one written.  *flag
-// (zero on entry) ends nonzero when some segment is heavy and the schedule was sorted;
-// keep_order != 0 keeps enumeration order (the flag stays zero, nothing is sorted).
-hipError_t fwd_plan(const FwdSlot *slots_host, int nslots, int64_t n_seg, int32_t *order,
-                    const int64_t *mcat_off, const int64_t *mcat_ld, int es, SegDesc *desc,
-                    int32_t *weight, uint32_t *flag, int keep_order, void *temp,
-                    hipStream_t s);
-// Flattened forward stream split into chunks of kFwdChunk weight (segments whole): cs has
-// nc_max + 2 entries, nc_max = fwd_chunk_bound(n_seg, sum of relation nnz); cs[c] = first
-// segment of chunk c, cs[nc_max + 1] = total weight.  temp: fwd_chunks_temp_bytes(n_seg);
-// `weight` may lie in temp past that size.
+// Slot table (copied to slots_dev), forward schedule and segment descriptors in schedule
+// order; mcat_off[t]: byte offset of Mcat_t in the workspace, mcat_ld[t]: its row length in
+// elements, es: element size.  weight[p] = balancing weight of segment p in the flattened
+// forward stream: the rows it moves, max(deg, 1) entries read plus one written.  *flag ends
+// nonzero when some segment is heavy and the schedule was sorted; keep_order != 0 keeps
+// enumeration order (the flag stays zero, nothing is sorted).  Then the flattened forward
+// stream split into chunks of kFwdChunk weight (segments whole): cs has nc_max + 2 entries,
+// nc_max = fwd_chunk_bound(n_seg, sum of relation nnz); cs[c] = first segment of chunk c,
+// cs[nc_max + 1] = total weight.  temp: fwd_chunks_temp_bytes(n_seg); `weight` may lie in
+// temp past that size.
+hipError_t fwd_plan(const FwdSlot *slots_host, int nslots, int64_t n_seg, FwdSlot *slots_dev,
+                    int32_t *order, const int64_t *mcat_off, const int64_t *mcat_ld, int es,
+                    SegDesc *desc, int32_t *weight, uint32_t *flag, int keep_order, int64_t nc_max,
+                    int32_t *cs, void *temp, hipStream_t s);
 int64_t fwd_chunk_bound(int64_t n_seg, int64_t nnz_total);
 size_t fwd_chunks_temp_bytes(int64_t n_seg);
-hipError_t fwd_chunks(const int32_t *weight, int64_t n_seg, int64_t nc_max, int32_t *cs,
-                      void *temp, hipStream_t s);
 // Combined transpose of several relations: one stable sort of all their edges by
 // key = koff_r + source row.  ip[key] (key in [0, key_range]) = position of the first edge
 // with that key; csd = destination rows in sorted order.  Relation r's transpose is
@@ -170,19 +168,26 @@ struct CscRels {
     int64_t koff[kMaxRels];
     int64_t e0[kMaxRels];         // position of the relation's first edge
 };
-hipError_t csc_build_all(const CscRels &rels, int64_t total_rows, int64_t nnz,
-                         int64_t key_range, int32_t *ip, int32_t *csd, void *temp,
-                         hipStream_t s);
-size_t csc_temp_bytes(int64_t nnz, int64_t key_range);
-struct BwdKeyRels {          // relations leaving one source type
-    int32_t count;
-    const int32_t *csc_indptr[kMaxRels];
+// The backward schedule of one source type: order is written; *flag ends nonzero when some
+// row is heavy and the schedule was sorted; rows of more than kSplitEdges transpose edges
+// are listed in split.  rel0, nrel: the relations leaving the type, in the list given beside.
+struct BwdType {
+    int64_t n;
+    int32_t *order;
+    uint32_t *flag;
+    SplitRows split;
+    int32_t rel0, nrel;
+    int32_t blk0, tile0, ntiles, hist;   // filled by bwd_plan
 };
-// *flag (zero on entry) ends nonzero when some row is heavy and the schedule was sorted;
-// keep_order != 0 keeps enumeration order.
-// Also lists the rows of more than kSplitEdges transpose edges in `split`.
-hipError_t bwd_schedule(const BwdKeyRels &rels, int64_t n_rows, int32_t *order, void *temp,
-                        uint32_t *flag, int keep_order, const SplitRows &split, hipStream_t s);
+// The transpose and the schedules of ntypes source types.  type_rels: the transpose offsets
+// (within ip) of each type's relations; max_nnz: edges of the largest relation; flags and
+// piece_counts: kMaxTypes words each, cleared here (the types' flags and piece counters
+// among them); keep_order != 0 keeps enumeration order.
+hipError_t bwd_plan(const CscRels &rels, int64_t total_rows, int64_t nnz, int64_t max_nnz,
+                    int64_t key_range, int32_t *ip, int32_t *csd, int ntypes, BwdType *types,
+                    const int32_t *const *type_rels, uint32_t *flags, uint32_t *piece_counts,
+                    int keep_order, void *temp, hipStream_t s);
+size_t csc_temp_bytes(int64_t nnz, int64_t key_range);
 hipError_t fill_words(void *dst, const void *src_host, size_t bytes, hipStream_t s);
 
 // aggregate.hip

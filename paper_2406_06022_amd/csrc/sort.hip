@@ -5,10 +5,6 @@
 #include "common.h"
 
 namespace rgcn {
-// exclusive scan whose kernels do nothing while *gate is zero (gate NULL: always run)
-hipError_t scan_gated(const int32_t *in, int32_t *out, int64_t n, void *temp,
-                      const uint32_t *gate, hipStream_t s);
-
 namespace {
 
 constexpr int kThreads = 256;
@@ -45,7 +41,7 @@ __device__ int wg_exclusive_scan(int v, int *total) {
     return below + x - v;
 }
 
-// ---------------------------------------------------------------- scan (3 kernels)
+// ---------------------------------------------------------------- scan (1 to 3 kernels)
 // A gate (NULL = none) is a device word: kernels given one do nothing while it is zero.
 // Tiles of 4096 values: in round u thread t holds values 4 (256 u + t) .. + 3 (one 16-byte
 // access when the arrays are 16-byte aligned, VEC), so every access of a round is
@@ -104,15 +100,69 @@ __global__ __launch_bounds__(kThreads) void k_scan_partials(int32_t *partial, in
     }
 }
 
-// partial NULL: a single tile (offset 0).  in may equal out: every value of a round is
-// read before that round's values are written.
-template <bool VEC>
-__global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t *in, int32_t *out,
-                                                         int64_t n, const int32_t *partial,
+// Where a scan's values go: out[i] (ChunkOut: the chunk starts of the forward stream, see
+// below, and no array of prefixes).
+struct ScanOut {
+    int32_t *out;
+    template <bool VEC>
+    __device__ __forceinline__ void put4(int64_t i, int64_t n, const int (&v)[4], const int (&o)[4],
+                                         const int32_t *) const {
+        if (VEC && i + 4 <= n) {
+            *(int4 *)(out + i) = make_int4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e < n) out[i + e] = o[e];
+        }
+    }
+};
+// Chunk starts of the flattened forward stream, from the exclusive prefix `o` of the segment
+// weights `v` (rows a segment moves).  Segment p belongs to chunk o / kFwdChunk; cs[c] is
+// the first segment of chunk c or later (chunks no segment starts in are empty), for
+// c <= ceil(total / kFwdChunk); cs[nc_max + 1] = total weight.
+struct ChunkOut {
+    int32_t *cs;
+    int64_t nc_max;
+    template <bool VEC>
+    __device__ __forceinline__ void put4(int64_t i, int64_t n, const int (&v)[4], const int (&o)[4],
+                                         const int32_t *in) const {
+        if (i >= n) return;
+        int64_t prev = i == 0 ? -1 : (int64_t)(o[0] - in[i - 1]) / kFwdChunk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t p = i + e;
+            if (p >= n) return;
+            const int64_t cur = o[e] / kFwdChunk;
+            for (int64_t c = prev + 1; c <= cur; ++c) cs[c] = (int32_t)p;
+            prev = cur;
+            if (p == n - 1) {
+                const int64_t total = (int64_t)o[e] + v[e];
+                const int64_t nc = (total + kFwdChunk - 1) / kFwdChunk;
+                for (int64_t c = cur + 1; c <= nc; ++c) cs[c] = (int32_t)n;
+                cs[nc_max + 1] = (int32_t)total;
+            }
+        }
+    }
+};
+
+// partial NULL: a single tile (offset 0); raw: the tiles' sums as k_scan_reduce left them,
+// of which the workgroup adds those before its own (otherwise their prefixes).  With
+// ScanOut, in may equal out: every value of a round is read before that round's values are
+// written.
+template <bool VEC, class Out>
+__global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t *in, Out out, int64_t n,
+                                                         const int32_t *partial, int raw,
                                                          const uint32_t *gate) {
     if (gated_off(gate)) return;
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int carry = partial ? partial[blockIdx.x] : 0;
+    int carry = 0;
+    if (partial && raw) {
+        int sum = 0;
+        for (int64_t i = threadIdx.x; i < blockIdx.x; i += kThreads) sum += partial[i];
+        wg_exclusive_scan(sum, &carry);
+    } else if (partial) {
+        carry = partial[blockIdx.x];
+    }
 #pragma unroll
     for (int u = 0; u < kScanRounds; ++u) {
         const int64_t i = base + 4 * ((int64_t)u * kThreads + threadIdx.x);
@@ -121,15 +171,43 @@ __global__ __launch_bounds__(kThreads) void k_scan_apply(const int32_t *in, int3
         int total;
         const int pre = wg_exclusive_scan(v[0] + v[1] + v[2] + v[3], &total) + carry;
         const int o[4] = {pre, pre + v[0], pre + v[0] + v[1], pre + v[0] + v[1] + v[2]};
-        if (VEC && i + 4 <= n) {
-            *(int4 *)(out + i) = make_int4(o[0], o[1], o[2], o[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (i + e < n) out[i + e] = o[e];
-        }
+        out.template put4<VEC>(i, n, v, o, in);
         carry += total;
     }
+}
+
+// Exclusive scan of in[0, n) into `out`; its kernels do nothing while *gate is zero (gate
+// NULL: always run).  One tile: the apply pass alone.  Up to kRawTiles tiles: the sums, then
+// the apply pass, whose workgroups add the sums before their own (a few KB from L2) where a
+// launch between the two took about 5 us; more tiles keep that launch.
+constexpr int64_t kRawTiles = 1024;
+template <class Out>
+hipError_t scan_to(const int32_t *in, const Out &out, int64_t n, void *temp, const uint32_t *gate,
+                   hipStream_t s, bool vec_out = true) {
+    if (n == 0) return hipSuccess;
+    const int64_t nb = cdiv(n, kScanTile);
+    const bool vec = ((uintptr_t)in % 16) == 0 && vec_out;
+    int32_t *partial = nb == 1 ? nullptr : (int32_t *)temp;
+    const dim3 grid((unsigned)nb), block(kThreads);
+    if (nb > 1) {
+        if (vec)
+            hipLaunchKernelGGL(k_scan_reduce<true>, grid, block, 0, s, in, n, partial, gate);
+        else
+            hipLaunchKernelGGL(k_scan_reduce<false>, grid, block, 0, s, in, n, partial, gate);
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+    const int raw = nb <= kRawTiles ? 1 : 0;
+    if (!raw) {
+        hipLaunchKernelGGL(k_scan_partials, dim3(1), block, 0, s, partial, nb, gate);
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+    if (vec)
+        hipLaunchKernelGGL((k_scan_apply<true, Out>), grid, block, 0, s, in, out, n,
+                           (const int32_t *)partial, raw, gate);
+    else
+        hipLaunchKernelGGL((k_scan_apply<false, Out>), grid, block, 0, s, in, out, n,
+                           (const int32_t *)partial, raw, gate);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- stable bucket sort
@@ -153,21 +231,17 @@ __global__ __launch_bounds__(kThreads) void k_bucket_hist(KeyFn kf, int64_t n, i
         hist[(int64_t)b * ntiles + blockIdx.x] = h[b];
 }
 
+// One tile's items to their places: run[b] (LDS) = position of the tile's first item of
+// key b.
 template <int NB, int BITS, class KeyFn, class PutFn>
-__global__ __launch_bounds__(kThreads) void k_bucket_scatter(KeyFn kf, PutFn put, int64_t n,
-                                                             const int32_t *offs,
-                                                             int32_t ntiles,
-                                                             const uint32_t *gate) {
-    if (gated_off(gate)) return;
-    __shared__ int32_t run[NB];
-    __shared__ int32_t wcnt[kThreads / 64][NB];
-    for (int b = threadIdx.x; b < NB; b += kThreads) {
-        run[b] = offs[(int64_t)b * ntiles + blockIdx.x];
+__device__ __forceinline__ void scatter_tile(const KeyFn &kf, const PutFn &put, int64_t n,
+                                             int64_t tile, int32_t (&run)[NB],
+                                             int32_t (&wcnt)[kThreads / 64][NB]) {
+    for (int b = threadIdx.x; b < NB; b += kThreads)
         for (int w = 0; w < kThreads / 64; ++w) wcnt[w][b] = 0;
-    }
     __syncthreads();
     const int wave = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
+    const int64_t base = tile * kSortTile;
     for (int u = 0; u < kSortItems; ++u) {
         const int64_t idx = base + (int64_t)u * kThreads + threadIdx.x;
         const bool valid = idx < n;
@@ -201,6 +275,47 @@ __global__ __launch_bounds__(kThreads) void k_bucket_scatter(KeyFn kf, PutFn put
 }
 
 template <int NB, int BITS, class KeyFn, class PutFn>
+__global__ __launch_bounds__(kThreads) void k_bucket_scatter(KeyFn kf, PutFn put, int64_t n,
+                                                             const int32_t *offs,
+                                                             int32_t ntiles,
+                                                             const uint32_t *gate) {
+    if (gated_off(gate)) return;
+    __shared__ int32_t run[NB];
+    __shared__ int32_t wcnt[kThreads / 64][NB];
+    for (int b = threadIdx.x; b < NB; b += kThreads) run[b] = offs[(int64_t)b * ntiles + blockIdx.x];
+    scatter_tile<NB, BITS>(kf, put, n, blockIdx.x, run, wcnt);
+}
+
+// First positions of a tile's items by schedule key, from the tiles' counts
+// (hist[b ntiles + t], counts as they are), added up by the workgroup: spares the scan's
+// launches where the counts are few (kSelfTiles).
+constexpr int kSelfTiles = 128;
+__device__ __forceinline__ void sched_run(const int32_t *hist, int32_t ntiles, int64_t tile,
+                                          int32_t (&run)[kSchedBuckets]) {
+    __shared__ int32_t tot[kSchedBuckets];
+    constexpr int L = kThreads / kSchedBuckets;   // lanes per bucket
+    const int b = threadIdx.x / L, l = threadIdx.x % L;
+    int all = 0, before = 0;
+    for (int t = l; t < ntiles; t += L) {
+        const int v = hist[(int64_t)b * ntiles + t];
+        all += v;
+        before += t < tile ? v : 0;
+    }
+    for (int o = L / 2; o > 0; o >>= 1) {
+        all += __shfl_xor(all, o, 64);
+        before += __shfl_xor(before, o, 64);
+    }
+    if (l == 0) tot[b] = all;
+    __syncthreads();
+    if (l == 0) {
+        int below = before;
+        for (int q = 0; q < b; ++q) below += tot[q];
+        run[b] = below;
+    }
+    __syncthreads();
+}
+
+template <int NB, int BITS, class KeyFn, class PutFn>
 hipError_t bucket_sort(const KeyFn &kf, const PutFn &put, int64_t n, void *temp,
                        hipStream_t s, const uint32_t *gate = nullptr) {
     if (n == 0) return hipSuccess;
@@ -210,7 +325,7 @@ hipError_t bucket_sort(const KeyFn &kf, const PutFn &put, int64_t n, void *temp,
     hipLaunchKernelGGL((k_bucket_hist<NB, KeyFn>), dim3((unsigned)ntiles), dim3(kThreads), 0,
                        s, kf, n, hist, (int32_t)ntiles, gate);
     RGCN_HIP_TRY(hipGetLastError());
-    RGCN_HIP_TRY(scan_gated(hist, hist, (int64_t)NB * ntiles, scan_tmp, gate, s));
+    RGCN_HIP_TRY(scan_to(hist, ScanOut{hist}, (int64_t)NB * ntiles, scan_tmp, gate, s));
     hipLaunchKernelGGL((k_bucket_scatter<NB, BITS, KeyFn, PutFn>), dim3((unsigned)ntiles),
                        dim3(kThreads), 0, s, kf, put, n, hist, (int32_t)ntiles, gate);
     return hipGetLastError();
@@ -225,54 +340,6 @@ __device__ __forceinline__ int degree_key(int64_t deg) {
     const int k = (kSchedBuckets - 2) - (lg - 5);
     return k > 0 ? k : 0;
 }
-
-// Forward segments: key of segment id = degree key of its (slot, row).
-struct FwdKey {
-    int32_t nslots;
-    int64_t base[kMaxSlots];
-    const int32_t *indptr[kMaxSlots];
-    __device__ int operator()(int64_t seg) const {
-        int lo = 0, hi = nslots - 1;           // last slot with base <= seg
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if (base[mid] <= seg) lo = mid; else hi = mid - 1;
-        }
-        const int32_t *ip = indptr[lo];
-        if (!ip) return degree_key(1);
-        int64_t row = seg - base[lo];
-        return degree_key((int64_t)ip[row + 1] - ip[row]);
-    }
-};
-
-struct PutIndex {
-    int32_t *order;
-    __device__ void operator()(int pos, int64_t idx) const { order[pos] = (int32_t)idx; }
-};
-
-// Backward rows of one source type: key = degree key of the in-degree summed over the
-// relations leaving the type.
-struct BwdKey {
-    BwdKeyRels rels;
-    // transpose degree of row j summed over the relations leaving the type
-    // (four relations' loads in flight at a time: past the last relation the first one is
-    // read again and not counted, so the loads need no branch)
-    __device__ int64_t degree(int64_t j) const {
-        int64_t deg = 0;
-        for (int r0 = 0; r0 < rels.count; r0 += 4) {
-            int32_t a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int32_t *ip = rels.csc_indptr[r0 + i < rels.count ? r0 + i : 0] + j;
-                a[i] = ip[0];
-                b[i] = ip[1];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) deg += r0 + i < rels.count ? (int64_t)b[i] - a[i] : 0;
-        }
-        return deg;
-    }
-    __device__ int operator()(int64_t j) const { return degree_key(degree(j)); }
-};
 
 // Radix pass: the digit (key >> shift) & mask.
 struct RadixKey {
@@ -352,17 +419,6 @@ __global__ __launch_bounds__(kThreads) void k_expand_edges(CscRels a, int64_t to
     }
 }
 
-// p[0, n) = v; 16-byte stores over the grid (p 16-byte aligned), a grid-stride loop
-__global__ __launch_bounds__(kThreads) void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
-    const int64_t n4 = n / 4;
-    const int4 q = make_int4(v, v, v, v);
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n4; i += stride)
-        ((int4 *)p)[i] = q;
-    const int64_t t = 4 * n4 + (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (t < n) p[t] = v;
-}
-
 // ---------------------------------------------------------------- CSC by placement
 // The per-key offsets are known from the counts, so each edge takes a slot of its key's
 // segment with one atomic decrement of the key's remaining count (cur, which returns to
@@ -389,13 +445,10 @@ __device__ __forceinline__ void cswap(int32_t &a, int32_t &b) {
     b = hi;
 }
 
-// One thread per key: segments of 2..kSegNet values sorted in registers (bitonic network
-// over 16 slots, unused slots +inf); longer segments are queued for k_csc_sort_long.
-__global__ __launch_bounds__(kThreads) void k_csc_sort_short(const int32_t *ip, int64_t nkeys,
-                                                             int32_t *csd, int32_t *long_keys,
-                                                             uint32_t *long_count) {
-    const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (k >= nkeys) return;
+// One thread per key k: segments of 2..kSegNet values sorted in registers (bitonic network
+// over 16 slots, unused slots +inf); longer segments are queued for sort_long.
+__device__ __forceinline__ void sort_short(int64_t k, const int32_t *ip, int32_t *csd,
+                                           int32_t *long_keys, uint32_t *long_count) {
     const int32_t b = ip[k], n = ip[k + 1] - b;
     if (n <= 1) return;
     if (n == 2) {
@@ -430,16 +483,15 @@ __global__ __launch_bounds__(kThreads) void k_csc_sort_short(const int32_t *ip, 
         if (i < n) csd[b + i] = v[i];
 }
 
-// One workgroup per queued segment (grid-stride over the queue): bitonic sort of up to
-// kSegLds values in LDS.  A longer segment raises *overflow, which runs the radix sort
-// of all edges instead.
-__global__ __launch_bounds__(kThreads) void k_csc_sort_long(const int32_t *ip, int32_t *csd,
-                                                            const int32_t *long_keys,
-                                                            const uint32_t *long_count,
-                                                            uint32_t *overflow) {
+// One workgroup per queued segment (workgroup wg of nwg): bitonic sort of up to kSegLds
+// values in LDS.  A longer segment raises *overflow, which runs the radix sort of all edges
+// instead.
+__device__ __forceinline__ void sort_long(int wg, int nwg, const int32_t *ip, int32_t *csd,
+                                          const int32_t *long_keys, const uint32_t *long_count,
+                                          uint32_t *overflow) {
     __shared__ int32_t buf[kSegLds];
     const uint32_t total = *long_count;
-    for (uint32_t q = blockIdx.x; q < total; q += gridDim.x) {
+    for (uint32_t q = wg; q < total; q += nwg) {
         const int32_t k = long_keys[q];
         const int32_t b = ip[k], n = ip[k + 1] - b;
         if (n > kSegLds) {
@@ -518,46 +570,142 @@ __device__ __forceinline__ int32_t desc_of(const DescArgs &a, int64_t seg, int64
     return d.deg;
 }
 
-// IDENT: schedule position p holds segment p; order[p] = p, and *flag is raised when some
-// segment is heavy (a schedule key other than the last), i.e. when the sorted schedule is
-// not the identity, unless `keep` asks for enumeration order.  Otherwise (gated on that
-// flag): segment order[p].
-// The slot tables are copied into LDS first: the slot search indexes them per lane, which
-// from the kernel arguments is a chain of dependent global loads.
-template <bool IDENT>
-__global__ __launch_bounds__(kThreads) void k_fwd_desc(DescArgs a, int32_t *order,
-                                                       int64_t n_seg, SegDesc *desc,
-                                                       int32_t *weight, uint32_t *flag, int keep) {
-    if (!IDENT && *flag == 0u) return;
-    __shared__ DescArgs s_a;
+// Enumeration order: schedule position p holds segment p.  *flag is raised when some segment
+// is heavy (a schedule key other than the last), i.e. when the sorted schedule is not the
+// identity, unless `keep` asks for enumeration order; hist[b ntiles + t] (zero before)
+// counts the keys of the sort's tiles on the way, so the sort needs no counting pass of its
+// own.  The slot tables are copied into LDS first: the slot search indexes them per lane,
+// which from the kernel arguments is a chain of dependent global loads.
+__device__ __forceinline__ void copy_desc(DescArgs *dst, const DescArgs &a) {
     static_assert(sizeof(DescArgs) % 4 == 0, "copied in words");
     for (int i = threadIdx.x; i < (int)(sizeof(DescArgs) / 4); i += kThreads)
-        ((uint32_t *)&s_a)[i] = ((const uint32_t *)&a)[i];
+        ((uint32_t *)dst)[i] = ((const uint32_t *)&a)[i];
+}
+__global__ __launch_bounds__(kThreads) void k_fwd_desc(DescArgs a, int32_t *order, int64_t n_seg,
+                                                       SegDesc *desc, int32_t *weight,
+                                                       uint32_t *flag, int keep, int32_t *hist,
+                                                       int32_t ntiles) {
+    __shared__ DescArgs s_a;
+    __shared__ int32_t h[kSchedBuckets];
+    copy_desc(&s_a, a);
+    if (threadIdx.x < kSchedBuckets) h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const bool in = p < n_seg;
-    int64_t seg = p;
-    if (!IDENT && in) seg = order[p];
-    if (IDENT && in) order[p] = (int32_t)p;
     bool heavy = false;
-    if (in) heavy = desc_of(s_a, seg, p, desc, weight) > 32;
-    if (IDENT && !keep && __ballot(heavy) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+    if (p < n_seg) {
+        order[p] = (int32_t)p;
+        const int key = degree_key(desc_of(s_a, p, p, desc, weight));
+        heavy = key != kSchedBuckets - 1;
+        if (!keep) atomicAdd(&h[key], 1);
+    }
+    if (keep) return;
+    if (__ballot(heavy) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+    __syncthreads();
+    const int t = (int)((int64_t)blockIdx.x * kThreads / kSortTile);
+    if (threadIdx.x < kSchedBuckets && h[threadIdx.x] > 0)
+        atomicAdd(&hist[threadIdx.x * ntiles + t], h[threadIdx.x]);
 }
 
-// Backward rows of one type in enumeration order (order[j] = j); *flag is raised when some
-// row is heavy, i.e. when the sorted schedule is not the identity, unless `keep` asks for
-// enumeration order.  Rows of more than kSplitEdges transpose edges are split into pieces
+// The sorted schedule, gated on *flag: segment ids and their descriptors at their places.
+struct FwdKey {
+    const DescArgs *a;   // LDS
+    __device__ int operator()(int64_t seg) const {
+        int lo = 0, hi = a->nslots - 1;           // last slot with base <= seg
+        while (lo < hi) {
+            int mid = (lo + hi + 1) >> 1;
+            if (a->base[mid] <= seg) lo = mid; else hi = mid - 1;
+        }
+        const int32_t *ip = a->indptr[lo];
+        if (!ip) return degree_key(1);
+        int64_t row = seg - a->base[lo];
+        return degree_key((int64_t)ip[row + 1] - ip[row]);
+    }
+};
+struct FwdPut {
+    const DescArgs *a;
+    int32_t *order;
+    SegDesc *desc;
+    int32_t *weight;
+    __device__ void operator()(int pos, int64_t seg) const {
+        order[pos] = (int32_t)seg;
+        desc_of(*a, seg, pos, desc, weight);
+    }
+};
+__global__ __launch_bounds__(kThreads) void k_fwd_sort(DescArgs a, int32_t *order, int64_t n_seg,
+                                                       SegDesc *desc, int32_t *weight,
+                                                       const int32_t *hist, int32_t ntiles,
+                                                       const uint32_t *flag) {
+    if (*flag == 0u) return;
+    __shared__ DescArgs s_a;
+    __shared__ int32_t run[kSchedBuckets];
+    __shared__ int32_t wcnt[kThreads / 64][kSchedBuckets];
+    copy_desc(&s_a, a);
+    if (ntiles <= kSelfTiles) {
+        sched_run(hist, ntiles, blockIdx.x, run);
+    } else {
+        if (threadIdx.x < kSchedBuckets)
+            run[threadIdx.x] = hist[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+        __syncthreads();
+    }
+    scatter_tile<kSchedBuckets, 5>(FwdKey{&s_a}, FwdPut{&s_a, order, desc, weight}, n_seg,
+                                   blockIdx.x, run, wcnt);
+}
+
+// The backward schedules of all types, one launch per stage.
+struct BwdTab {
+    int32_t ntypes;
+    const int32_t *csc_indptr[kMaxRels];   // by type: the relations leaving it
+    BwdType type[kMaxTypes];
+};
+// transpose degree of row j summed over the relations leaving the type
+// (four relations' loads in flight at a time: past the last relation the first one is
+// read again and not counted, so the loads need no branch)
+__device__ __forceinline__ int64_t bwd_degree(const int32_t *const *rels, int nrel, int64_t j) {
+    int64_t deg = 0;
+    for (int r0 = 0; r0 < nrel; r0 += 4) {
+        int32_t a[4], b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int32_t *ip = rels[r0 + i < nrel ? r0 + i : 0] + j;
+            a[i] = ip[0];
+            b[i] = ip[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) deg += r0 + i < nrel ? (int64_t)b[i] - a[i] : 0;
+    }
+    return deg;
+}
+struct BwdKey {
+    const int32_t *const *rels;
+    int nrel;
+    __device__ int operator()(int64_t j) const { return degree_key(bwd_degree(rels, nrel, j)); }
+};
+struct PutIndex {
+    int32_t *order;
+    __device__ void operator()(int pos, int64_t idx) const { order[pos] = (int32_t)idx; }
+};
+
+// Rows of one type in enumeration order (order[j] = j); its flag is raised when some row is
+// heavy, i.e. when the sorted schedule is not the identity, unless `keep` asks for
+// enumeration order, and the keys of the sort's tiles are counted (types of more than one
+// tile).  Rows of more than kSplitEdges transpose edges are split into pieces
 // of kSplitEdges edges: np[j] = their count (0 for other rows), and the pieces (j, 0),
 // (j, 1), ... take consecutive slots from the shared counter (the slots' places vary from
 // run to run; what is summed, and in which order, does not).
-__global__ __launch_bounds__(kThreads) void k_bwd_ident(BwdKey kf, int64_t n, int32_t *order,
-                                                        uint32_t *flag, int keep, SplitRows sp) {
-    const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const bool in = j < n;
-    int64_t deg = 0;
-    if (in) {
-        order[j] = (int32_t)j;
-        deg = kf.degree(j);
+__device__ __forceinline__ void bwd_ident(const BwdTab &tab, int wg, int keep, int32_t *hist) {
+    __shared__ int32_t h[kSchedBuckets];
+    int t = 0;
+    for (int i = 1; i < tab.ntypes; ++i) t = tab.type[i].blk0 <= wg ? i : t;
+    const BwdType &ty = tab.type[t];
+    const bool count = !keep && ty.ntiles > 1;
+    if (threadIdx.x < kSchedBuckets) h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t j = (int64_t)(wg - ty.blk0) * kThreads + threadIdx.x;
+    bool heavy = false;
+    if (j < ty.n) {
+        ty.order[j] = (int32_t)j;
+        const int64_t deg = bwd_degree(tab.csc_indptr + ty.rel0, ty.nrel, j);
+        const SplitRows &sp = ty.split;
         const int32_t np = deg > kSplitEdges ? (int32_t)((deg + kSplitEdges - 1) / kSplitEdges) : 0;
         sp.np[j] = np;
         if (np > 0) {
@@ -568,29 +716,107 @@ __global__ __launch_bounds__(kThreads) void k_bwd_ident(BwdKey kf, int64_t n, in
             if ((int64_t)b + np <= sp.cap)
                 for (int32_t q = 0; q < np; ++q) sp.pieces[b + q] = make_int2((int)j, q);
         }
+        const int key = degree_key(deg);
+        heavy = !keep && key != kSchedBuckets - 1;
+        if (count) atomicAdd(&h[key], 1);
     }
-    const bool heavy = in && !keep && degree_key(deg) != kSchedBuckets - 1;
-    if (__ballot(heavy) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
+    if (__ballot(heavy) != 0 && (threadIdx.x & 63) == 0) atomicOr(ty.flag, 1u);
+    if (!count) return;   // the whole workgroup
+    __syncthreads();
+    const int tile = (int)((int64_t)(wg - ty.blk0) * kThreads / kSortTile);
+    if (threadIdx.x < kSchedBuckets && h[threadIdx.x] > 0)
+        atomicAdd(&hist[ty.hist + threadIdx.x * ty.ntiles + tile], h[threadIdx.x]);
 }
 
-
-// Chunk starts of the flattened forward stream.  pre = exclusive prefix of the segment
-// weights (rows a segment moves).  Segment p belongs to chunk pre[p] / kFwdChunk; cs[c] is
-// the first segment of chunk c or later (chunks no segment starts in are empty), for
-// c <= ceil(total / kFwdChunk); cs[nc_max + 1] = total weight.
-__global__ __launch_bounds__(kThreads) void k_chunk_starts(const int32_t *pre, const int32_t *weight,
-                                                           int64_t n_seg, int64_t nc_max, int32_t *cs) {
-    const int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (p >= n_seg) return;
-    const int64_t cur = pre[p] / kFwdChunk;
-    const int64_t prev = p == 0 ? -1 : pre[p - 1] / kFwdChunk;
-    for (int64_t c = prev + 1; c <= cur; ++c) cs[c] = (int32_t)p;
-    if (p == n_seg - 1) {
-        const int64_t total = (int64_t)pre[p] + weight[p];
-        const int64_t nc = (total + kFwdChunk - 1) / kFwdChunk;
-        for (int64_t c = cur + 1; c <= nc; ++c) cs[c] = (int32_t)n_seg;
-        cs[nc_max + 1] = (int32_t)total;
+// Second-to-last stage of the backward plan: the transpose's short segments sorted (nshort
+// workgroups, one thread per key), and beside them every type's rows in enumeration order.
+__global__ __launch_bounds__(kThreads) void k_bwd_rows(int nshort, const int32_t *ip, int64_t nkeys,
+                                                       int32_t *csd, int32_t *long_keys,
+                                                       uint32_t *long_count, BwdTab tab, int keep,
+                                                       int32_t *hist) {
+    if ((int)blockIdx.x < nshort) {
+        const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+        if (k < nkeys) sort_short(k, ip, csd, long_keys, long_count);
+    } else {
+        bwd_ident(tab, (int)blockIdx.x - nshort, keep, hist);
     }
+}
+
+// Last stage: the queued long segments (nlong workgroups), and the schedules of the types
+// whose flag is raised.
+__global__ __launch_bounds__(kThreads) void k_bwd_sort(int nlong, const int32_t *ip, int32_t *csd,
+                                                       const int32_t *long_keys,
+                                                       const uint32_t *long_count,
+                                                       uint32_t *overflow, BwdTab tab,
+                                                       const int32_t *hist) {
+    if ((int)blockIdx.x < nlong) {
+        sort_long((int)blockIdx.x, nlong, ip, csd, long_keys, long_count, overflow);
+        return;
+    }
+    const int wg = (int)blockIdx.x - nlong;
+    int t = 0;
+    for (int i = 1; i < tab.ntypes; ++i) t = tab.type[i].tile0 <= wg ? i : t;
+    const BwdType &ty = tab.type[t];
+    if (*ty.flag == 0u) return;
+    __shared__ int32_t run[kSchedBuckets];
+    __shared__ int32_t wcnt[kThreads / 64][kSchedBuckets];
+    const BwdKey kf{tab.csc_indptr + ty.rel0, ty.nrel};
+    const int64_t tile = wg - ty.tile0;
+    if (ty.ntiles == 1) {          // its keys were not counted
+        if (threadIdx.x < kSchedBuckets) wcnt[0][threadIdx.x] = 0;
+        __syncthreads();
+        for (int64_t j = threadIdx.x; j < ty.n; j += kThreads) atomicAdd(&wcnt[0][kf(j)], 1);
+        __syncthreads();
+        if (threadIdx.x < kSchedBuckets) {
+            int below = 0;
+            for (int b = 0; b < (int)threadIdx.x; ++b) below += wcnt[0][b];
+            run[threadIdx.x] = below;
+        }
+        __syncthreads();
+    } else if (ty.ntiles <= kSelfTiles) {
+        sched_run(hist + ty.hist, ty.ntiles, tile, run);
+    } else {
+        if (threadIdx.x < kSchedBuckets)
+            run[threadIdx.x] = hist[ty.hist + (int64_t)threadIdx.x * ty.ntiles + tile];
+        __syncthreads();
+    }
+    scatter_tile<kSchedBuckets, 5>(kf, PutIndex{ty.order}, ty.n, tile, run, wcnt);
+}
+
+// Start of the forward plan: the slot table, the schedule's flag, the key counts.  Slots past
+// the kernel arguments' room take further launches of k_fill_words.
+constexpr int kInitSlots = 64;
+struct InitSlots {
+    int32_t n;
+    FwdSlot slot[kInitSlots];
+};
+__global__ __launch_bounds__(kThreads) void k_fwd_init(InitSlots a, FwdSlot *slots, uint32_t *flag,
+                                                       int32_t *hist, int64_t nhist) {
+    const int64_t i0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (blockIdx.x == 0) {
+        const int words = a.n * (int)(sizeof(FwdSlot) / 4);
+        for (int i = threadIdx.x; i < words; i += kThreads)
+            ((uint32_t *)slots)[i] = ((const uint32_t *)a.slot)[i];
+        if (threadIdx.x == 0) *flag = 0u;
+    }
+    for (int64_t i = i0; i < nhist; i += (int64_t)gridDim.x * kThreads) hist[i] = 0;
+}
+
+// Start of the backward plan: p[0, n) = 0 (16-byte stores, p 16-byte aligned), and the
+// schedule flags and piece counters of all types.
+__global__ __launch_bounds__(kThreads) void k_bwd_init(int32_t *p, int64_t n, uint32_t *flags,
+                                                       uint32_t *pieces) {
+    if (blockIdx.x == 0 && threadIdx.x < kMaxTypes) {
+        flags[threadIdx.x] = 0u;
+        pieces[threadIdx.x] = 0u;
+    }
+    const int64_t n4 = n / 4;
+    const int4 q = make_int4(0, 0, 0, 0);
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n4; i += stride)
+        ((int4 *)p)[i] = q;
+    const int64_t t = 4 * n4 + (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (t < n) p[t] = 0;
 }
 
 struct Words {
@@ -605,42 +831,9 @@ __global__ void k_fill_words(uint32_t *dst, Words a) {
 
 size_t scan_temp_bytes(int64_t n) { return align_up((size_t)cdiv(n, kScanTile) * 4 + 4, 256); }
 
-hipError_t scan_gated(const int32_t *in, int32_t *out, int64_t n, void *temp,
-                      const uint32_t *gate, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    const int64_t nb = cdiv(n, kScanTile);
-    const bool vec = ((uintptr_t)in % 16) == 0 && ((uintptr_t)out % 16) == 0;
-    if (nb == 1) {   // one tile: the apply pass alone
-        if (vec)
-            hipLaunchKernelGGL(k_scan_apply<true>, dim3(1), dim3(kThreads), 0, s, in, out, n,
-                               (const int32_t *)nullptr, gate);
-        else
-            hipLaunchKernelGGL(k_scan_apply<false>, dim3(1), dim3(kThreads), 0, s, in, out, n,
-                               (const int32_t *)nullptr, gate);
-        return hipGetLastError();
-    }
-    int32_t *partial = (int32_t *)temp;
-    if (vec)
-        hipLaunchKernelGGL(k_scan_reduce<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, in, n,
-                           partial, gate);
-    else
-        hipLaunchKernelGGL(k_scan_reduce<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, in, n,
-                           partial, gate);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kThreads), 0, s, partial, nb, gate);
-    RGCN_HIP_TRY(hipGetLastError());
-    if (vec)
-        hipLaunchKernelGGL(k_scan_apply<true>, dim3((unsigned)nb), dim3(kThreads), 0, s, in, out,
-                           n, (const int32_t *)partial, gate);
-    else
-        hipLaunchKernelGGL(k_scan_apply<false>, dim3((unsigned)nb), dim3(kThreads), 0, s, in, out,
-                           n, (const int32_t *)partial, gate);
-    return hipGetLastError();
-}
-
 hipError_t exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, void *temp,
                               hipStream_t s) {
-    return scan_gated(in, out, n, temp, nullptr, s);
+    return scan_to(in, ScanOut{out}, n, temp, nullptr, s, ((uintptr_t)out % 16) == 0);
 }
 
 size_t bucket_sort_temp_bytes(int64_t n, int nbuckets) {
@@ -649,18 +842,30 @@ size_t bucket_sort_temp_bytes(int64_t n, int nbuckets) {
            scan_temp_bytes((int64_t)nbuckets * ntiles);
 }
 
-hipError_t fwd_plan(const FwdSlot *slots_host, int nslots, int64_t n_seg, int32_t *order,
-                    const int64_t *mcat_off, const int64_t *mcat_ld, int es, SegDesc *desc,
-                    int32_t *weight, uint32_t *flag, int keep_order, void *temp,
-                    hipStream_t s) {
+hipError_t fwd_plan(const FwdSlot *slots_host, int nslots, int64_t n_seg, FwdSlot *slots_dev,
+                    int32_t *order, const int64_t *mcat_off, const int64_t *mcat_ld, int es,
+                    SegDesc *desc, int32_t *weight, uint32_t *flag, int keep_order, int64_t nc_max,
+                    int32_t *cs, void *temp, hipStream_t s) {
+    InitSlots init;
+    init.n = nslots < kInitSlots ? nslots : kInitSlots;
+    for (int i = 0; i < init.n; ++i) init.slot[i] = slots_host[i];
+    const int64_t ntiles = cdiv(n_seg, kSortTile);
+    int32_t *hist = (int32_t *)temp;
+    const int64_t nhist = keep_order ? 0 : kSchedBuckets * ntiles;
+    int64_t blocks = cdiv(nhist, kThreads * 4);
+    blocks = blocks < 1 ? 1 : (blocks > 256 ? 256 : blocks);
+    hipLaunchKernelGGL(k_fwd_init, dim3((unsigned)blocks), dim3(kThreads), 0, s, init, slots_dev,
+                       flag, hist, nhist);
+    RGCN_HIP_TRY(hipGetLastError());
+    if (nslots > kInitSlots)
+        RGCN_HIP_TRY(fill_words(slots_dev + kInitSlots, slots_host + kInitSlots,
+                                sizeof(FwdSlot) * (nslots - kInitSlots), s));
     if (n_seg == 0) return hipSuccess;
     DescArgs a;
     a.nslots = nslots;
-    FwdKey kf;
-    kf.nslots = nslots;
     for (int i = 0; i < kMaxSlots; ++i) {
-        a.base[i] = kf.base[i] = i < nslots ? slots_host[i].seg_base : 0;
-        a.indptr[i] = kf.indptr[i] = i < nslots ? slots_host[i].indptr : nullptr;
+        a.base[i] = i < nslots ? slots_host[i].seg_base : 0;
+        a.indptr[i] = i < nslots ? slots_host[i].indptr : nullptr;
         a.dst[i] = (int16_t)(i < nslots ? slots_host[i].dst_type : 0);
         a.col_off[i] = i < nslots ? slots_host[i].col_off : 0;
     }
@@ -669,16 +874,20 @@ hipError_t fwd_plan(const FwdSlot *slots_host, int nslots, int64_t n_seg, int32_
         a.mcat_ld[t] = mcat_ld[t];
     }
     a.es = es;
-    const dim3 grid((unsigned)cdiv(n_seg, kThreads));
-    // enumeration order first; the sort and the second descriptor pass run only when some
-    // segment is heavy (otherwise the stable sort by key is the identity)
-    hipLaunchKernelGGL(k_fwd_desc<true>, grid, dim3(kThreads), 0, s, a, order, n_seg, desc,
-                       weight, flag, keep_order);
+    // enumeration order first; the sort runs only when some segment is heavy (otherwise the
+    // stable sort by key is the identity)
+    hipLaunchKernelGGL(k_fwd_desc, dim3((unsigned)cdiv(n_seg, kThreads)), dim3(kThreads), 0, s, a,
+                       order, n_seg, desc, weight, flag, keep_order, hist, (int32_t)ntiles);
     RGCN_HIP_TRY(hipGetLastError());
-    RGCN_HIP_TRY((bucket_sort<kSchedBuckets, 5>(kf, PutIndex{order}, n_seg, temp, s, flag)));
-    hipLaunchKernelGGL(k_fwd_desc<false>, grid, dim3(kThreads), 0, s, a, order, n_seg, desc,
-                       weight, flag, keep_order);
-    return hipGetLastError();
+    void *scan_tmp = (char *)temp + align_up((size_t)kSchedBuckets * ntiles * 4, 256);
+    if (!keep_order) {
+        if (ntiles > kSelfTiles)
+            RGCN_HIP_TRY(scan_to(hist, ScanOut{hist}, nhist, scan_tmp, flag, s));
+        hipLaunchKernelGGL(k_fwd_sort, dim3((unsigned)ntiles), dim3(kThreads), 0, s, a, order, n_seg,
+                           desc, weight, hist, (int32_t)ntiles, flag);
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+    return scan_to(weight, ChunkOut{cs, nc_max}, n_seg, scan_tmp, nullptr, s);
 }
 
 int64_t fwd_chunk_bound(int64_t n_seg, int64_t nnz_total) {
@@ -687,26 +896,6 @@ int64_t fwd_chunk_bound(int64_t n_seg, int64_t nnz_total) {
 
 size_t fwd_chunks_temp_bytes(int64_t n_seg) {
     return 2 * align_up((size_t)n_seg * 4 + 4, 256) + scan_temp_bytes(n_seg);
-}
-
-hipError_t fwd_chunks(const int32_t *weight, int64_t n_seg, int64_t nc_max, int32_t *cs,
-                      void *temp, hipStream_t s) {
-    if (n_seg == 0) return hipSuccess;
-    int32_t *pre = (int32_t *)temp;
-    void *stemp = (char *)temp + align_up((size_t)n_seg * 4 + 4, 256);
-    RGCN_HIP_TRY(exclusive_scan_i32(weight, pre, n_seg, stemp, s));
-    hipLaunchKernelGGL(k_chunk_starts, dim3((unsigned)cdiv(n_seg, kThreads)), dim3(kThreads), 0, s,
-                       pre, weight, n_seg, nc_max, cs);
-    return hipGetLastError();
-}
-
-hipError_t bwd_schedule(const BwdKeyRels &rels, int64_t n_rows, int32_t *order, void *temp,
-                        uint32_t *flag, int keep_order, const SplitRows &split, hipStream_t s) {
-    if (n_rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bwd_ident, dim3((unsigned)cdiv(n_rows, kThreads)), dim3(kThreads), 0, s,
-                       BwdKey{rels}, n_rows, order, flag, keep_order, split);
-    RGCN_HIP_TRY(hipGetLastError());
-    return bucket_sort<kSchedBuckets, 5>(BwdKey{rels}, PutIndex{order}, n_rows, temp, s, flag);
 }
 
 // Digit plan of an LSD radix sort of keys < key_range: the fewest passes of at most 10
@@ -734,10 +923,15 @@ size_t csc_temp_bytes(int64_t nnz, int64_t key_range) {
 // per key), offsets by an exclusive scan of the counts, each edge placed in its key's
 // segment, segments sorted by value.  If some segment is longer than kSegLds, the LSD
 // radix sort of all pairs (stable, digits of at most 10 bits) runs instead, gated on a
-// device flag so the host never waits.
-hipError_t csc_build_all(const CscRels &rels, int64_t total_rows, int64_t nnz,
-                         int64_t key_range, int32_t *ip, int32_t *csd, void *temp,
-                         hipStream_t s) {
+// device flag so the host never waits; its launches are left out where no relation has
+// that many edges.  The schedules of the types ride along: rows and key counts beside the
+// short segments' sort, the sorts beside the long segments'.  (A launch whose work is gated
+// off takes about 4 us all the same; a block's backward plan took some 30 of them, and on a
+// small mini-batch they were the longest chain of the step.)
+hipError_t bwd_plan(const CscRels &rels, int64_t total_rows, int64_t nnz, int64_t max_nnz,
+                    int64_t key_range, int32_t *ip, int32_t *csd, int ntypes, BwdType *types,
+                    const int32_t *const *type_rels, uint32_t *flags, uint32_t *piece_counts,
+                    int keep_order, void *temp, hipStream_t s) {
     int passes, bits;
     radix_plan(key_range, &passes, &bits);
     if (nnz == 0) passes = 0;
@@ -747,35 +941,76 @@ hipError_t csc_build_all(const CscRels &rels, int64_t total_rows, int64_t nnz,
     const size_t arr = align_up((size_t)nnz * 4 + 4, 256);
     int32_t *tmp_vals = (int32_t *)temp;
     uint32_t *kb[2] = {(uint32_t *)((char *)temp + arr), (uint32_t *)((char *)temp + 2 * arr)};
-    void *sort_tmp = (char *)temp + 3 * arr;   // also the scan's scratch
+    void *sort_tmp = (char *)temp + 3 * arr;   // also the scans' scratch
     int32_t *cur = (int32_t *)((char *)sort_tmp + align_up(sort > scan ? sort : scan, 256));
     uint32_t *words = (uint32_t *)(cur + key_range + 1);   // queue length, overflow
     int32_t *long_keys = (int32_t *)kb[0];                 // at most nnz / (kSegNet + 1)
 
     // cursors and the two words start at zero
-    {
-        int64_t blocks = cdiv(cdiv(key_range + 3, 4), kThreads);
-        blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
-        hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)blocks), dim3(kThreads), 0, s, cur,
-                           key_range + 3, 0);
-    }
+    const int64_t nzero = key_range > 0 ? key_range + 3 : 0;
+    int64_t blocks = cdiv(cdiv(nzero, 4), kThreads);
+    blocks = blocks < 1 ? 1 : (blocks > 2048 ? 2048 : blocks);
+    hipLaunchKernelGGL(k_bwd_init, dim3((unsigned)blocks), dim3(kThreads), 0, s, cur, nzero, flags,
+                       piece_counts);
     RGCN_HIP_TRY(hipGetLastError());
-    if (total_rows > 0 && nnz > 0) {
-        hipLaunchKernelGGL(k_expand_edges, dim3((unsigned)cdiv(total_rows, kThreads)),
-                           dim3(kThreads), 0, s, rels, total_rows, kb[1], tmp_vals, cur);
+    if (key_range > 0) {
+        if (total_rows > 0 && nnz > 0) {
+            hipLaunchKernelGGL(k_expand_edges, dim3((unsigned)cdiv(total_rows, kThreads)),
+                               dim3(kThreads), 0, s, rels, total_rows, kb[1], tmp_vals, cur);
+            RGCN_HIP_TRY(hipGetLastError());
+        }
+        RGCN_HIP_TRY(exclusive_scan_i32(cur, ip, key_range + 1, sort_tmp, s));
+        if (nnz > 0) {
+            hipLaunchKernelGGL(k_csc_place, dim3((unsigned)cdiv(nnz, kThreads)), dim3(kThreads), 0,
+                               s, kb[1], tmp_vals, nnz, ip, cur, csd);
+            RGCN_HIP_TRY(hipGetLastError());
+        }
+    }
+    // every cursor is back at zero: their space counts the schedule keys of the types of
+    // more than one tile (32 counts per 4,096 rows; such a type has a cursor for every row
+    // and relation leaving it, and without relations all its rows are light)
+    int32_t *hist = cur;
+    BwdTab tab;
+    tab.ntypes = 0;
+    int64_t nblk = 0, ntile = 0, nh = 0;
+    int nr = 0;
+    for (int i = 0; i < ntypes; ++i) {
+        BwdType t = types[i];
+        if (t.n == 0) continue;
+        for (int r = 0; r < t.nrel; ++r) tab.csc_indptr[nr + r] = type_rels[t.rel0 + r];
+        t.rel0 = nr;
+        nr += t.nrel;
+        t.blk0 = (int32_t)nblk;
+        nblk += cdiv(t.n, kThreads);
+        t.ntiles = t.nrel > 0 ? (int32_t)cdiv(t.n, kSortTile) : 1;
+        t.tile0 = (int32_t)ntile;
+        ntile += t.ntiles;
+        t.hist = (int32_t)nh;
+        if (t.ntiles > 1) nh += (int64_t)kSchedBuckets * t.ntiles;
+        tab.type[tab.ntypes++] = t;
+    }
+    const int64_t nshort = nnz > 0 ? cdiv(key_range, kThreads) : 0;
+    if (nshort + nblk > 0) {
+        hipLaunchKernelGGL(k_bwd_rows, dim3((unsigned)(nshort + nblk)), dim3(kThreads), 0, s,
+                           (int)nshort, ip, key_range, csd, long_keys, words, tab, keep_order, hist);
         RGCN_HIP_TRY(hipGetLastError());
     }
-    RGCN_HIP_TRY(exclusive_scan_i32(cur, ip, key_range + 1, sort_tmp, s));
-    if (nnz == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_csc_place, dim3((unsigned)cdiv(nnz, kThreads)), dim3(kThreads), 0, s,
-                       kb[1], tmp_vals, nnz, ip, cur, csd);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_csc_sort_short, dim3((unsigned)cdiv(key_range, kThreads)), dim3(kThreads),
-                       0, s, ip, key_range, csd, long_keys, words);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_csc_sort_long, dim3(512), dim3(kThreads), 0, s, ip, csd, long_keys,
-                       words, words + 1);
-    RGCN_HIP_TRY(hipGetLastError());
+    if (nnz == 0) return hipSuccess;   // no segment to sort, every row light
+    if (keep_order) ntile = 0;
+    for (int i = 0; i < tab.ntypes && !keep_order; ++i)
+        if (tab.type[i].ntiles > kSelfTiles) {
+            int32_t *h = hist + tab.type[i].hist;
+            RGCN_HIP_TRY(scan_to(h, ScanOut{h}, (int64_t)kSchedBuckets * tab.type[i].ntiles,
+                                 sort_tmp, tab.type[i].flag, s));
+        }
+    // no key has more edges than the largest relation
+    const int64_t nlong = max_nnz > kSegNet ? 512 : 0;
+    if (nlong + ntile > 0) {
+        hipLaunchKernelGGL(k_bwd_sort, dim3((unsigned)(nlong + ntile)), dim3(kThreads), 0, s,
+                           (int)nlong, ip, csd, long_keys, words, words + 1, tab, hist);
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+    if (max_nnz <= kSegLds) return hipSuccess;
 
     // fallback, gated on the overflow word: values ping-pong between tmp_vals and csd
     // from tmp_vals; with an even number of passes they end in tmp_vals and are copied
