@@ -1078,33 +1078,56 @@ __global__ __launch_bounds__(kThreads) void k_transpose_pipe_adagrad(TsumArgs a,
 }
 
 // WcatT[n][s*d_in + c] = W_s[c][n]: the forward transform's weights, K-contiguous.
-struct WSlots {
-    const void *w[kMaxSlots];
-};
-// The slots stacked as one [K x d_out] matrix (row kk = s d_in + c) are transposed in
-// 64 x 64 tiles through LDS: a tile's rows are read along n and written along kk, so both
-// sides are whole contiguous pieces; the padded LDS row keeps the column reads off one
-// bank.
+// The slots of a type stacked as one [K x d_out] matrix (row kk = s d_in + c) are transposed
+// in 64 x 64 tiles through LDS, all types of a block in one launch: a tile's rows are read
+// along n and written along kk, 16 bytes per lane on both sides (d_in, d_out and every row
+// are whole 16-byte chunks).  LDS pitch: the 64 / VEC chunks and the rows that a wave reads
+// together fall on distinct banks.  Latency-bound: a type took a launch of 11 us with 2-byte
+// accesses, a block's four types now 7 us together.
 constexpr int kPackTile = 64;
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_pack_weights(WSlots ws, int nslots, int d_in,
-                                                           int d_out, T *out) {
-    __shared__ T tile[kPackTile][kPackTile + 1];
-    const int K = nslots * d_in;
-    const int kk0 = blockIdx.x * kPackTile, n0 = blockIdx.y * kPackTile;
-    const int tx = threadIdx.x % kPackTile, ty = threadIdx.x / kPackTile;
-    constexpr int kRowsPerPass = kThreads / kPackTile;
-    for (int r = ty; r < kPackTile; r += kRowsPerPass) {
-        const int kk = kk0 + r, n = n0 + tx;
+__global__ __launch_bounds__(kThreads) void k_pack_weights(PackTab tab, int d_in, int d_out) {
+    constexpr int VEC = 16 / (int)sizeof(T);
+    constexpr int CPR = kPackTile / VEC;                       // chunks per tile row
+    constexpr int P = sizeof(T) == 2 ? kPackTile + 2 : kPackTile + 1;
+    constexpr int ROUNDS = kPackTile * CPR / kThreads;
+    __shared__ __attribute__((aligned(16))) T tile[kPackTile * P];
+    int t = 0;
+    for (int i = 1; i < tab.ntypes; ++i) t = tab.type[i].tile0 <= (int)blockIdx.x ? i : t;
+    const PackType ty = tab.type[t];
+    const int K = ty.nslots * d_in;
+    const int kk0 = ((int)blockIdx.x - ty.tile0) * kPackTile, n0 = blockIdx.y * kPackTile;
+    u32x4 v[ROUNDS];
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int idx = threadIdx.x + i * kThreads;
+        const int kk = kk0 + idx / CPR, n = n0 + idx % CPR * VEC;
+        v[i] = u32x4{0u, 0u, 0u, 0u};
         if (kk < K && n < d_out) {
             const int sl = kk / d_in, c = kk - sl * d_in;
-            tile[r][tx] = ((const T *)ws.w[sl])[(int64_t)c * d_out + n];
+            v[i] = *(const u32x4 *)((const T *)tab.w[ty.slot0 + sl] + (int64_t)c * d_out + n);
         }
     }
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int idx = threadIdx.x + i * kThreads;
+        uint32_t *d = (uint32_t *)(tile + idx / CPR * P + idx % CPR * VEC);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = v[i][e];
+    }
     __syncthreads();
-    for (int r = ty; r < kPackTile; r += kRowsPerPass) {
-        const int n = n0 + r, kk = kk0 + tx;
-        if (n < d_out && kk < K) out[(int64_t)n * K + kk] = tile[tx][r];
+#pragma unroll
+    for (int i = 0; i < ROUNDS; ++i) {
+        const int idx = threadIdx.x + i * kThreads;
+        const int r = idx / CPR, c = idx % CPR * VEC;
+        const int n = n0 + r, kk = kk0 + c;
+        if (n >= d_out || kk >= K) continue;
+        T o[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o[e] = tile[(c + e) * P + r];
+        u32x4 w;
+        __builtin_memcpy(&w, o, 16);
+        *(u32x4 *)((T *)ty.wcat + (int64_t)n * K + kk) = w;
     }
 }
 
@@ -1397,19 +1420,18 @@ hipError_t transpose_sum(rgcn_dtype dt, const TsumArgs &a, hipStream_t s) {
                            : transpose_sum_dt<false>(a, gs, chunks, s);
 }
 
-hipError_t pack_weights(rgcn_dtype dt, int d_in, int d_out, const void *const *w_slots,
-                        int nslots, void *wcat_t, hipStream_t s) {
-    WSlots ws;
-    for (int i = 0; i < kMaxSlots; ++i) ws.w[i] = i < nslots ? w_slots[i] : nullptr;
-    const int64_t K = (int64_t)nslots * d_in;
-    if (K == 0 || d_out == 0) return hipSuccess;
-    const dim3 grid((unsigned)cdiv(K, kPackTile), (unsigned)cdiv(d_out, kPackTile));
+hipError_t pack_weights(rgcn_dtype dt, int d_in, int d_out, PackTab &tab, hipStream_t s) {
+    int64_t tiles = 0;
+    for (int t = 0; t < tab.ntypes; ++t) {
+        tab.type[t].tile0 = (int32_t)tiles;
+        tiles += cdiv((int64_t)tab.type[t].nslots * d_in, kPackTile);
+    }
+    if (tiles == 0 || d_out == 0) return hipSuccess;
+    const dim3 grid((unsigned)tiles, (unsigned)cdiv(d_out, kPackTile));
     if (dt == RGCN_BF16)
-        hipLaunchKernelGGL(k_pack_weights<uint16_t>, grid, dim3(kThreads), 0, s, ws, nslots, d_in,
-                           d_out, (uint16_t *)wcat_t);
+        hipLaunchKernelGGL(k_pack_weights<uint16_t>, grid, dim3(kThreads), 0, s, tab, d_in, d_out);
     else
-        hipLaunchKernelGGL(k_pack_weights<float>, grid, dim3(kThreads), 0, s, ws, nslots, d_in,
-                           d_out, (float *)wcat_t);
+        hipLaunchKernelGGL(k_pack_weights<float>, grid, dim3(kThreads), 0, s, tab, d_in, d_out);
     return hipGetLastError();
 }
 

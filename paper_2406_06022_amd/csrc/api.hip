@@ -556,21 +556,29 @@ rgcn_status rgcn_block_transform(const rgcn_block *block, const rgcn_params *par
     if ((st = check_workspace(L, workspace, workspace_bytes)) != RGCN_OK) return st;
     if ((st = check_forward_outputs(block, L.T, y, relu_mask, flags)) != RGCN_OK) return st;
     char *ws = (char *)workspace;
+    // weights of each type, K-contiguous: [W_self_t; W_r for r into t] transposed
+    PackTab pack;
+    FwdGemm gemm[kMaxTypes];
+    pack.ntypes = 0;
+    int slots = 0;
     for (int t = 0; t < L.T; ++t) {
         if (block->n_dst[t] == 0) continue;
-        // weights of type t, K-contiguous: [W_self_t; W_r for r into t] transposed
-        const void *wslots[kMaxSlots];
-        wslots[0] = params->w_self[t];
+        PackType &pt = pack.type[pack.ntypes];
+        pt.wcat = ws + L.off_wcat[t];
+        pt.slot0 = slots;
+        pt.nslots = L.type_nslots[t];
+        pack.w[slots] = params->w_self[t];
         for (int r = 0; r < L.R; ++r)
-            if (L.rel_pos[r] > 0 && block->rels[r].dst_type == t) wslots[L.rel_pos[r]] = params->w_rel[r];
-        TRY_HIP(pack_weights(L.dt, L.d_in, L.d_out, wslots, L.type_nslots[t], ws + L.off_wcat[t],
-                             stream), "pack weights");
-        const void *bias = params->bias ? params->bias[t] : nullptr;
-        TRY_HIP(gemm_forward(L.dt, ws + L.off_mcat[t], block->n_dst[t], L.d_out, (int)L.K[t],
-                             ws + L.off_wcat[t], bias, (flags & RGCN_FUSE_RELU) ? 1 : 0, y[t],
-                             relu_mask ? relu_mask[t] : nullptr, stream),
-                "forward transform");
+            if (L.rel_pos[r] > 0 && block->rels[r].dst_type == t)
+                pack.w[slots + L.rel_pos[r]] = params->w_rel[r];
+        slots += pt.nslots;
+        gemm[pack.ntypes++] = FwdGemm{ws + L.off_mcat[t], block->n_dst[t], (int32_t)L.K[t], pt.wcat,
+                                      params->bias ? params->bias[t] : nullptr, y[t],
+                                      relu_mask ? relu_mask[t] : nullptr};
     }
+    TRY_HIP(pack_weights(L.dt, L.d_in, L.d_out, pack, stream), "pack weights");
+    TRY_HIP(gemm_forward(L.dt, gemm, pack.ntypes, L.d_out, (flags & RGCN_FUSE_RELU) ? 1 : 0, stream),
+            "forward transform");
     return RGCN_OK;
 }
 

@@ -311,8 +311,19 @@ struct FeatArgs {
 // range, skipped)
 hipError_t featureless_mean(const FeatArgs &a, uint32_t *words, hipStream_t s);
 
-hipError_t pack_weights(rgcn_dtype dt, int d_in, int d_out, const void *const *w_slots,
-                        int nslots, void *wcat_t, hipStream_t s);
+// The forward weights of each destination type, packed K-contiguous at wcat: slots
+// w[slot0 .. slot0 + nslots) of the shared list.
+struct PackType {
+    void *wcat;
+    int32_t slot0, nslots;
+    int32_t tile0;            // filled by pack_weights
+};
+struct PackTab {
+    int32_t ntypes;
+    PackType type[kMaxTypes];
+    const void *w[kMaxSlots];
+};
+hipError_t pack_weights(rgcn_dtype dt, int d_in, int d_out, PackTab &tab, hipStream_t s);
 // hilo: dy rows in the hi/lo form (cols bf16 high parts, then cols low parts); cols a
 // multiple of 4, dy and partial 16-byte aligned.  partial: temp_bytes of temporary space, at
 // least column_sums_temp_bytes (more of it is used as more, shorter row ranges).
@@ -328,11 +339,19 @@ hipError_t validate_src_rows(const int32_t *indices, const int64_t *rows, int64_
                              hipStream_t s);
 
 // gemm.hip
-// Forward: Y = A W + bias (opt. ReLU); A [M x K] row-major (ld K), wcat_t [N x K].
-// mask (or NULL): the positive bits of the stored Y, [M x ceil(N / 64)] words.
-hipError_t gemm_forward(rgcn_dtype dt, const void *a, int64_t M, int N, int K,
-                        const void *wcat_t, const void *bias, int relu, void *y,
-                        uint64_t *mask, hipStream_t s);
+// Forward, per destination type: Y = A W + bias (opt. ReLU); A [M x K] row-major (ld K),
+// wcat_t [N x K].  mask (or NULL): the positive bits of the stored Y, [M x ceil(N / 64)]
+// words.
+struct FwdGemm {
+    const void *a;
+    int64_t M;
+    int32_t K;
+    const void *wcat_t;
+    const void *bias;
+    void *y;
+    uint64_t *mask;
+};
+hipError_t gemm_forward(rgcn_dtype dt, const FwdGemm *g, int ntypes, int N, int relu, hipStream_t s);
 // Backward input side: C[m][n] = (sum_k dy[m][k] W_slot(n)[c(n)][k]) / deg_slot(n)(m);
 // slot(n) = n / d_in, c(n) = n % d_in; indptr[slot] NULL: no scaling (self-loop slot).
 struct DmsSlots {

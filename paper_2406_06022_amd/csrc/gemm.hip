@@ -509,7 +509,7 @@ struct EpiDmsFwd {
     int32_t N;
     int32_t kwrap;
     uint32_t inv_din;
-    const int32_t *indptr[kMaxSlots];
+    int32_t slot0;            // the type's first slot in the table's indptr list
 };
 
 // dMs rows divided by the segment's degree.  The degrees a lane's epilogue needs are read
@@ -765,10 +765,33 @@ __device__ __forceinline__ void vm_wait_barrier() {
 // columns of one row: the epilogue stores straight from registers, and LDS holds only the
 // pipeline stages.  Steps past the last tile load zero tiles, so every step issues the
 // same loads; everything lands before a workgroup exits.
+// One launch takes the products of all types of a block: each type has a range of the
+// workgroups (multiples of 8, so its XCD mapping is that of a launch of its own), sized by
+// fwd_shares.  (A launch per type left most CUs idle wherever a type has fewer tiles than
+// CUs, and at each launch's last tiles everywhere else.)
+template <class E>
+struct FwdTab {
+    int32_t ntypes;
+    struct Type {
+        const char *a, *b;
+        int64_t lda, ldb, M, N, K;
+        E epi;
+        int32_t tiles_m, tiles_n, wg0, nwg;
+    } type[kMaxTypes];
+    // input-side form: segment offsets of the slots of all types (NULL: the self slot)
+    const int32_t *indptr[E::kDms ? kMaxSlots : 1];
+};
 template <class C, int BK, int S, class E>
-__global__ __launch_bounds__(C::NT, C::NT / 256) void k_gemm_fwd(
-    const char *__restrict__ a, int64_t lda, int64_t M, const char *__restrict__ b,
-    int64_t ldb, int64_t N, int64_t K, const E epi, int64_t tiles_m, int64_t tiles_n) {
+__global__ __launch_bounds__(C::NT, C::NT / 256) void k_gemm_fwd(const FwdTab<E> tab) {
+    int ty = 0;
+    for (int i = 1; i < tab.ntypes; ++i) ty = tab.type[i].wg0 <= (int)blockIdx.x ? i : ty;
+    const char *__restrict__ a = tab.type[ty].a;
+    const char *__restrict__ b = tab.type[ty].b;
+    const int64_t lda = tab.type[ty].lda, ldb = tab.type[ty].ldb;
+    const int64_t M = tab.type[ty].M, N = tab.type[ty].N, K = tab.type[ty].K;
+    const E epi = tab.type[ty].epi;
+    const int64_t tiles_m = tab.type[ty].tiles_m, tiles_n = tab.type[ty].tiles_n;
+    const int bid = (int)blockIdx.x - tab.type[ty].wg0, nwg = tab.type[ty].nwg;
     using Gm = DlGeom<BK>;
     constexpr int FM = C::FM, FN = C::FN, NW = C::NT / 64;
     constexpr int A_BYTES = C::TM * Gm::RB, B_BYTES = C::TN * Gm::RB;
@@ -784,9 +807,9 @@ __global__ __launch_bounds__(C::NT, C::NT / 256) void k_gemm_fwd(
     __shared__ __attribute__((aligned(1024))) char lds[SA * A_BYTES + SB * B_BYTES];
 
     const int64_t T = tiles_m * tiles_n;
-    const int64_t wpx = (int64_t)gridDim.x / 8;          // workgroups per XCD (grid % 8 == 0)
+    const int64_t wpx = nwg / 8;                         // workgroups per XCD (nwg % 8 == 0)
     const int64_t per = (T + 7) / 8;
-    const int64_t x = blockIdx.x % 8, jx = blockIdx.x / 8;
+    const int64_t x = bid % 8, jx = bid / 8;
     const int64_t lo = x * per + jx, hi = (x + 1) * per < T ? (x + 1) * per : T;
     const int64_t ntile = lo < hi ? (hi - lo + wpx - 1) / wpx : 0;
     const int64_t nk = (K + BK - 1) / BK;
@@ -888,7 +911,7 @@ __global__ __launch_bounds__(C::NT, C::NT / 256) void k_gemm_fwd(
                 // no segments or the row is outside the output)
                 const int64_t nw = n0 + wn * FN * 16;
                 const int sl = nw < N ? (int)__umulhi((uint32_t)nw, epi.inv_din) : 0;
-                const int32_t *ip = nw < N ? epi.indptr[sl] : nullptr;
+                const int32_t *ip = nw < N ? tab.indptr[epi.slot0 + sl] : nullptr;
 #pragma unroll
                 for (int mi = 0; mi < FM; ++mi) {
                     const int64_t m = m0 + wm * FM * 16 + mi * 16 + r16;
@@ -925,7 +948,7 @@ __global__ __launch_bounds__(C::NT, C::NT / 256) void k_gemm_fwd(
                 // 16 ni + 4 (lane / 16) .. + 3, stored as they are (16 bytes)
                 const int64_t nw = n0 + wn * FN * 16;
                 const int sl = nw < N ? (int)__umulhi((uint32_t)nw, epi.inv_din) : 0;
-                const bool seg = nw < N && epi.indptr[sl] != nullptr;
+                const bool seg = nw < N && tab.indptr[epi.slot0 + sl] != nullptr;
 #pragma unroll
                 for (int mi = 0; mi < FM; ++mi) {
                     const int64_t m = m0 + wm * FM * 16 + mi * 16 + r16;
@@ -1512,32 +1535,91 @@ constexpr int kDmsRegStages = 1;
 
 }  // namespace
 
-hipError_t gemm_forward(rgcn_dtype dt, const void *a, int64_t M, int N, int K,
-                        const void *wcat_t, const void *bias, int relu, void *y,
-                        uint64_t *mask, hipStream_t s) {
-    const ReluMask rm{mask, (int64_t)(N + 63) / 64};
-    if (dt == RGCN_BF16) {
-        using C = CfgFwd;
-        const int64_t tiles_m = cdiv(M, C::TM), tiles_n = cdiv(N, C::TN);
-        if (tiles_m == 0 || tiles_n == 0) return hipSuccess;
-        // one workgroup per CU (a multiple of 8 so every XCD has the same count)
-        int64_t P = tiles_m * tiles_n;
-        const int64_t cus = device_cus();
-        if (P > cus) P = cus;
-        P = (P + 7) / 8 * 8;
-        hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, EpiForwardBf16>), dim3((unsigned)P),
-                           dim3(C::NT), 0, s, (const char *)a, (int64_t)K * 2, M,
-                           (const char *)wcat_t, (int64_t)K * 2, (int64_t)N, (int64_t)K,
-                           EpiForwardBf16{y, bias, M, N, relu, rm}, tiles_m, tiles_n);
-        return hipGetLastError();
-    }
+static hipError_t gemm_forward_f32(const FwdGemm &g, int N, int relu, hipStream_t s) {
     using C = CfgF32;
     using TL = TileF32;
-    LoadRows<TL, C::NT, PlainRows> la{PlainRows{(const char *)a, (int64_t)K * 4, M}, (int64_t)K * 4};
-    LoadRows<TL, C::NT, PlainRows> lb{PlainRows{(const char *)wcat_t, (int64_t)K * 4, N},
-                                      (int64_t)K * 4};
+    LoadRows<TL, C::NT, PlainRows> la{PlainRows{(const char *)g.a, (int64_t)g.K * 4, g.M},
+                                      (int64_t)g.K * 4};
+    LoadRows<TL, C::NT, PlainRows> lb{PlainRows{(const char *)g.wcat_t, (int64_t)g.K * 4, N},
+                                      (int64_t)g.K * 4};
+    const ReluMask rm{g.mask, (int64_t)(N + 63) / 64};
     return launch_gemm<C, MmaF32<C::FM, C::FN>, decltype(la), decltype(lb), EpiForward<false>, 2, 2>(
-        la, lb, EpiForward<false>{y, bias, M, N, relu, rm}, M, N, K, 1, K, s);
+        la, lb, EpiForward<false>{g.y, g.bias, g.M, N, relu, rm}, g.M, N, g.K, 1, g.K, s);
+}
+
+// Workgroups of each type in a grouped launch of k_gemm_fwd, in groups of 8 (one per XCD):
+// a workgroup per tile where the tiles of all types fit the device; otherwise the device's
+// workgroups (one per CU) handed out one group at a time to the type whose workgroups have
+// the most left to do (tiles each, times the steps and the epilogue of a tile).
+template <class Tab>
+int64_t fwd_shares(Tab &tab, int bk) {
+    int64_t groups = device_cus() / 8, used = 0, need = 0;
+    if (groups < 1) groups = 1;
+    int64_t tiles[kMaxTypes], cap[kMaxTypes], share[kMaxTypes];
+    for (int t = 0; t < tab.ntypes; ++t) {
+        tiles[t] = (int64_t)tab.type[t].tiles_m * tab.type[t].tiles_n;
+        cap[t] = cdiv(tiles[t], 8);
+        need += cap[t];
+        share[t] = 1;
+        ++used;
+    }
+    if (need <= groups) {
+        for (int t = 0; t < tab.ntypes; ++t) share[t] = cap[t];
+        used = groups;
+    }
+    for (; used < groups; ++used) {
+        int best = -1;
+        double most = 0.;
+        for (int t = 0; t < tab.ntypes; ++t) {
+            if (share[t] >= cap[t]) continue;
+            const double load = (double)cdiv(tiles[t], 8 * share[t]) *
+                                (double)(cdiv(tab.type[t].K, bk) + 3);
+            if (load > most) {
+                most = load;
+                best = t;
+            }
+        }
+        if (best < 0) break;
+        ++share[best];
+    }
+    int64_t wg = 0;
+    for (int t = 0; t < tab.ntypes; ++t) {
+        tab.type[t].wg0 = (int32_t)wg;
+        tab.type[t].nwg = (int32_t)(8 * share[t]);
+        wg += 8 * share[t];
+    }
+    return wg;
+}
+
+hipError_t gemm_forward(rgcn_dtype dt, const FwdGemm *g, int ntypes, int N, int relu,
+                        hipStream_t s) {
+    if (dt == RGCN_BF16) {
+        using C = CfgFwd;
+        FwdTab<EpiForwardBf16> tab;
+        tab.ntypes = 0;
+        for (int t = 0; t < ntypes; ++t) {
+            if (g[t].M == 0 || N == 0) continue;
+            auto &ty = tab.type[tab.ntypes++];
+            ty.a = (const char *)g[t].a;
+            ty.b = (const char *)g[t].wcat_t;
+            ty.lda = ty.ldb = (int64_t)g[t].K * 2;
+            ty.M = g[t].M;
+            ty.N = N;
+            ty.K = g[t].K;
+            ty.epi = EpiForwardBf16{g[t].y, g[t].bias, g[t].M, N, relu,
+                                    ReluMask{g[t].mask, (int64_t)(N + 63) / 64}};
+            ty.tiles_m = (int32_t)cdiv(g[t].M, C::TM);
+            ty.tiles_n = (int32_t)cdiv(N, C::TN);
+        }
+        if (tab.ntypes == 0) return hipSuccess;
+        const int64_t P = fwd_shares(tab, kFwdBK);
+        hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, EpiForwardBf16>), dim3((unsigned)P),
+                           dim3(C::NT), 0, s, tab);
+        return hipGetLastError();
+    }
+    for (int t = 0; t < ntypes; ++t)
+        RGCN_HIP_TRY(gemm_forward_f32(g[t], N, relu, s));
+    return hipSuccess;
 }
 
 hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int d_out,
@@ -1559,21 +1641,25 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
         hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)pb), dim3(kThreads), 0, s, sr, chunks,
                            d_out / 8, (u32x4 *)wpack);
         RGCN_HIP_TRY(hipGetLastError());
-        EpiDmsFwd e{};
-        e.out = dms;
-        e.M = M;
-        e.N = (int32_t)N;
-        e.kwrap = d_out;
-        e.inv_din = (uint32_t)(((1ull << 32) + (uint64_t)d_in - 1) / (uint64_t)d_in);
-        for (int i = 0; i < kMaxSlots; ++i) e.indptr[i] = i < slots.count ? slots.indptr[i] : nullptr;
-        int64_t P = tiles_m * tiles_n;
-        const int64_t cus = device_cus();
-        if (P > cus) P = cus;
-        P = (P + 7) / 8 * 8;
+        FwdTab<EpiDmsFwd> tab;
+        tab.ntypes = 1;
+        auto &ty = tab.type[0];
+        ty.a = (const char *)dy;
+        ty.b = (const char *)wpack;
+        ty.lda = (int64_t)d_out * 4;
+        ty.ldb = (int64_t)d_out * 2;
+        ty.M = M;
+        ty.N = N;
+        ty.K = (int64_t)d_out * 2;
+        ty.epi = EpiDmsFwd{dms, M, (int32_t)N, d_out,
+                           (uint32_t)(((1ull << 32) + (uint64_t)d_in - 1) / (uint64_t)d_in), 0};
+        ty.tiles_m = (int32_t)tiles_m;
+        ty.tiles_n = (int32_t)tiles_n;
+        for (int i = 0; i < kMaxSlots; ++i)
+            tab.indptr[i] = i < slots.count ? slots.indptr[i] : nullptr;
+        const int64_t P = fwd_shares(tab, kFwdBK);
         hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, EpiDmsFwd>), dim3((unsigned)P),
-                           dim3(C::NT), 0, s, (const char *)dy, (int64_t)d_out * 4, M,
-                           (const char *)wpack, (int64_t)d_out * 2, N, (int64_t)d_out * 2, e,
-                           tiles_m, tiles_n);
+                           dim3(C::NT), 0, s, tab);
         return hipGetLastError();
     }
     EpiDms epi;
