@@ -93,6 +93,9 @@ struct Layout {
     size_t plan_temp = 0;
     size_t off_dms[kMaxTypes];          // relative to scratch
     size_t off_partial = 0, off_colsum = 0;
+    // the least workspace, and what a workspace of the size reported holds beyond it: room
+    // for the weight-gradient partials of all types at once
+    size_t total_min = 0, dw_room = 0;
     size_t total = 0;
 };
 
@@ -324,15 +327,26 @@ rgcn_status make_layout(const rgcn_block *b, const rgcn_params *p, Layout &L) {
     L.off_partial = bt;   bt += align256(part);
     L.off_colsum = bt;    bt += align256(cols);
     L.off_split_partial = bt;  bt += align256((size_t)L.piece_total * L.d_in * 4 + 16);
-    L.total = L.off_scratch + (L.plan_temp > bt ? L.plan_temp : bt);
+    L.total_min = L.total = L.off_scratch + (L.plan_temp > bt ? L.plan_temp : bt);
+    DwGemm dw[kMaxTypes];
+    int ndw = 0;
+    for (int t = 0; t < L.T; ++t)
+        if (b->n_dst[t] > 0)
+            dw[ndw++] = DwGemm{nullptr, b->n_dst[t], (int32_t)L.K[t], nullptr, 0, L.type_nslots[t]};
+    const size_t want = align256(gemm_dw_room(L.dt, dw, ndw, L.d_out));
+    if (want > L.off_split_partial - L.off_partial) {
+        L.dw_room = want;
+        L.total += want;
+    }
     return RGCN_OK;
 }
 
 rgcn_status check_workspace(const Layout &L, void *ws, size_t bytes) {
     if (!ws) return fail(RGCN_ERR_INVALID_ARG, "workspace is NULL");
     if ((uintptr_t)ws & 255u) return fail(RGCN_ERR_INVALID_ARG, "workspace not 256-byte aligned");
-    if (bytes < L.total)
-        return fail(RGCN_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", bytes, L.total);
+    if (bytes < L.total_min)
+        return fail(RGCN_ERR_WORKSPACE_TOO_SMALL, "workspace %zu bytes, need %zu", bytes,
+                    L.total_min);
     return RGCN_OK;
 }
 
@@ -654,39 +668,66 @@ rgcn_status rgcn_block_backward_dense(const rgcn_block *block, const rgcn_params
                     return fail(RGCN_ERR_INVALID_ARG, "dw_self[%d] aliases dw_self[%d]", t, u);
     char *ws = (char *)workspace;
     char *scratch = ws + L.off_scratch;
+    // weight side: [dW_self_t; dW_r ...] = Mcat_t^T dY_t; zeros for the weights into a type
+    // without rows.  The space of the partial sums and the column sums' own behind it
+    const size_t room = L.off_split_partial - L.off_partial;
+    DwGemm dw[kMaxTypes];
+    float *dw_out[kMaxSlots];
+    int ndw = 0, nslots = 0;
     for (int t = 0; t < L.T; ++t) {
         const int64_t nd = block->n_dst[t];
-        // weight side: [dW_self_t; dW_r ...] = Mcat_t^T dY_t
-        DwOut out{};
-        out.count = nd > 0 ? L.type_nslots[t] : 1;
-        out.w[0] = dw_self ? dw_self[t] : nullptr;
-        bool any = out.w[0] != nullptr;
-        if (nd > 0) {
-            for (int r = 0; r < L.R; ++r)
-                if (L.rel_pos[r] > 0 && block->rels[r].dst_type == t) {
-                    out.w[L.rel_pos[r]] = dw_rel ? dw_rel[r] : nullptr;
-                    any |= out.w[L.rel_pos[r]] != nullptr;
-                }
-        } else {  // no rows: gradients of the weights into t are zero
-            for (int r = 0; r < L.R; ++r)
-                if (block->rels[r].dst_type == t && dw_rel && dw_rel[r] && out.count < kMaxSlots) {
-                    out.w[out.count++] = dw_rel[r];
-                    any = true;
-                }
-        }
-        if (any)
-            TRY_HIP(gemm_dw(L.dt, nd > 0 ? ws + L.off_mcat[t] : nullptr, nd,
-                            nd > 0 ? (int)L.K[t] : out.count * L.d_in, L.d_in,
-                            nd > 0 ? dy[t] : nullptr, hilo, L.d_out, out,
-                            (float *)(scratch + L.off_partial), stream), "weight gradient");
+        int count = 1;
+        float **out = dw_out + nslots;
+        out[0] = dw_self ? dw_self[t] : nullptr;
+        bool any = out[0] != nullptr;
+        for (int r = 0; r < L.R; ++r)
+            if (block->rels[r].dst_type == t) {
+                float *w = dw_rel ? dw_rel[r] : nullptr;
+                out[nd > 0 ? L.rel_pos[r] : count] = w;
+                ++count;
+                any |= w != nullptr;
+            }
+        if (!any) continue;
+        dw[ndw++] = DwGemm{nd > 0 ? ws + L.off_mcat[t] : nullptr, nd, count * L.d_in,
+                           nd > 0 ? dy[t] : nullptr, nslots, count};
+        nslots += count;
+    }
+    // (a workspace of the size reported has room for all types' sums at its end)
+    const bool roomy = L.dw_room > 0 && workspace_bytes >= L.total;
+    TRY_HIP(gemm_dw(L.dt, dw, ndw, dw_out, L.d_in, hilo, L.d_out,
+                    (float *)(roomy ? ws + L.total_min : scratch + L.off_partial),
+                    roomy ? L.dw_room : room, stream), "weight gradient");
+    // input side in fp32: all types in one launch
+    DmsGemm dms32[kMaxTypes];
+    const void *dms_w[kMaxSlots];
+    const int32_t *dms_ip[kMaxSlots];
+    int ndms = 0, ndslots = 0;
+    for (int t = 0; t < L.T; ++t) {
+        const int64_t nd = block->n_dst[t];
         if (dbias && dbias[t])
             // the weight-gradient partials are reduced by now: their space and the column
             // sums' own behind it serve the row ranges' sums
             TRY_HIP(column_sums(nd > 0 ? dy[t] : nullptr, hilo, nd, L.d_out, dbias[t],
-                                (float *)(scratch + L.off_partial),
-                                L.off_split_partial - L.off_partial, stream), "bias gradient");
+                                (float *)(scratch + L.off_partial), room, stream), "bias gradient");
         // input side: dMs_t = dY_t [W_self_t | W_r ...]^T, relation slots divided by deg
         if (nd > 0 && L.dms_nslots[t] > 0) {
+            if (L.dt == RGCN_F32) {
+                const void **w32 = dms_w + ndslots;
+                const int32_t **ip32 = dms_ip + ndslots;
+                if (L.dms_self[t] >= 0) {
+                    w32[L.dms_self[t]] = params->w_self[t];
+                    ip32[L.dms_self[t]] = nullptr;
+                }
+                for (int r = 0; r < L.R; ++r)
+                    if (L.dms_rel[r] >= 0 && block->rels[r].dst_type == t) {
+                        w32[L.dms_rel[r]] = params->w_rel[r];
+                        ip32[L.dms_rel[r]] = block->rels[r].indptr;
+                    }
+                dms32[ndms++] = DmsGemm{dy[t], nd, (float *)(scratch + L.off_dms[t]), ndslots,
+                                        L.dms_nslots[t]};
+                ndslots += L.dms_nslots[t];
+                continue;
+            }
             DmsSlots ds{};
             ds.count = L.dms_nslots[t];
             if (L.dms_self[t] >= 0) {
@@ -705,6 +746,9 @@ rgcn_status rgcn_block_backward_dense(const rgcn_block *block, const rgcn_params
                     "input-side transform");
         }
     }
+    if (ndms > 0)
+        TRY_HIP(gemm_dms_f32(dms32, ndms, L.d_out, L.d_in, dms_w, dms_ip, stream),
+                "input-side transform");
     return RGCN_OK;
 }
 

@@ -363,16 +363,33 @@ struct DmsSlots {
 // packed when dy is in the hi/lo form), or NULL
 hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int d_out,
                     int d_in, const DmsSlots &slots, float *dms, void *wpack, hipStream_t s);
+// The same in fp32, all types in one launch: slots w / indptr[slot0 .. slot0 + count) of the
+// shared lists.
+struct DmsGemm {
+    const float *dy;
+    int64_t M;
+    float *dms;
+    int32_t slot0, count;
+};
+hipError_t gemm_dms_f32(const DmsGemm *g, int ntypes, int d_out, int d_in, const void *const *w,
+                        const int32_t *const *indptr, hipStream_t s);
 // Weight side: dWcat[kc][o] = sum_i Mcat[i][kc] dy[i][o], K = rows of Mcat.
 size_t gemm_dw_partial_bytes(int64_t M, int Kcat, int d_out);
-struct DwOut {
-    int32_t count;            // slots
-    float *w[kMaxSlots];      // destination of slot s ([d_in x d_out]) or NULL
+// One destination type's weight gradient: slots w[slot0 .. slot0 + count) of the shared list
+// (an entry NULL: not wanted); M = 0: zeros.
+struct DwGemm {
+    const void *mcat;
+    int64_t M;
+    int32_t Kcat;             // count * d_in
+    const float *dy;
+    int32_t slot0, count;
 };
-// dy_hilo (bf16): dy rows in the hi/lo form (d_out bf16 high parts, then d_out low parts)
-hipError_t gemm_dw(rgcn_dtype dt, const void *mcat, int64_t M, int Kcat, int d_in,
-                   const float *dy, bool dy_hilo, int d_out, const DwOut &out, float *partial,
-                   hipStream_t s);
+// dy_hilo (bf16): dy rows in the hi/lo form (d_out bf16 high parts, then d_out low parts).
+// partial: `room` bytes of temporary space, at least gemm_dw_partial_bytes of every type;
+// gemm_dw_room: what lets all types split as far as the device has workgroups.
+size_t gemm_dw_room(rgcn_dtype dt, const DwGemm *g, int ntypes, int d_out);
+hipError_t gemm_dw(rgcn_dtype dt, const DwGemm *g, int ntypes, float *const *w, int d_in,
+                   bool dy_hilo, int d_out, float *partial, size_t room, hipStream_t s);
 
 }  // namespace rgcn
 

@@ -62,6 +62,8 @@ using CfgDms = CfgNarrow;   // bf16 input side: N is one or two slots of d_in co
 using CfgDw = CfgWide;
 constexpr int kDwMinWaves = CfgDw::NT / 64 / 4;   // waves per SIMD
 using CfgF32 = Cfg<128, 128, 2, 2>;
+using CfgF32Small = Cfg<64, 64, 4, 1>;
+constexpr int kF32BK = 32;   // K elements per step of the fp32 products
 
 template <int ROWS_, int BK_, int ES_>
 struct Tile {
@@ -75,7 +77,7 @@ struct Tile {
     static_assert((PITCH / 16) % 2 == 1, "pitch must be an odd number of 16-byte units");
 };
 template <class C> using TileBf16 = Tile<C::TM, 64, 2>;
-using TileF32 = Tile<CfgF32::TM, 16, 4>;
+template <class C> using TileF32 = Tile<C::TM, 32, 4>;
 
 // Register staging uses the compiler's native vector types (one 16-byte load or LDS store,
 // no struct copies).
@@ -125,33 +127,36 @@ struct MmaBf16SplitA32 {
     }
 };
 
-// fp32: lane group q holds k = 4q..4q+3 of its row; MFMA step s uses element s, so the
-// four steps together cover k = 0..15 (the sum over k is taken in a different order, not
-// a different set).
-template <int FM, int FN>
+// fp32: of each 16 K values lane group q holds k = 4q..4q+3 of its row; MFMA step s uses
+// element s, so the four steps together cover k = 0..15 (the sum over k is taken in a
+// different order, not a different set).
+template <class TL, int FM, int FN>
 struct MmaF32 {
-    using T = TileF32;
+    using T = TL;
     using Acc = f32x4;
     static constexpr int AM = FM, AN = FN;
     static constexpr int STAGE_BYTES = 2 * T::BYTES;
     __device__ __forceinline__ static void run(const char *As, const char *Bs,
                                                f32x4 (&acc)[FM][FN], int wm, int wn, int lane) {
-        f32x4 a[FM], b[FN];
         const int r = lane & 15, q = lane >> 4;
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
-            a[i] = *(const f32x4 *)(As + (wm * FM * 16 + i * 16 + r) * T::PITCH + q * 16);
+        for (int kk = 0; kk < T::BK / 16; ++kk) {
+            f32x4 a[FM], b[FN];
 #pragma unroll
-        for (int i = 0; i < FN; ++i)
-            b[i] = *(const f32x4 *)(Bs + (wn * FN * 16 + i * 16 + r) * T::PITCH + q * 16);
+            for (int i = 0; i < FM; ++i)
+                a[i] = *(const f32x4 *)(As + (wm * FM * 16 + i * 16 + r) * T::PITCH + kk * 64 + q * 16);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+            for (int i = 0; i < FN; ++i)
+                b[i] = *(const f32x4 *)(Bs + (wn * FN * 16 + i * 16 + r) * T::PITCH + kk * 64 + q * 16);
 #pragma unroll
-            for (int mi = 0; mi < FM; ++mi)
+            for (int s = 0; s < 4; ++s)
 #pragma unroll
-                for (int ni = 0; ni < FN; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mi][s], b[ni][s],
-                                                                       acc[mi][ni], 0, 0, 0);
+                for (int mi = 0; mi < FM; ++mi)
+#pragma unroll
+                    for (int ni = 0; ni < FN; ++ni)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mi][s], b[ni][s],
+                                                                           acc[mi][ni], 0, 0, 0);
+        }
     }
 };
 
@@ -166,8 +171,11 @@ struct PlainRows {
         return base + (r < rows ? r : rows - 1) * ld_bytes;
     }
 };
-struct SlotRows {  // row n = (slot n / d_in, column c = n % d_in) of W_slot [d_in x d_out]
-    const void *w[kMaxSlots];
+// row n = (slot n / d_in, column c = n % d_in) of W_slot [d_in x d_out]; List: the slots'
+// weights, held here or elsewhere in the kernel's arguments
+template <class List>
+struct SlotRowsOf {
+    List w;
     int32_t d_in;
     int32_t es_dout;   // bytes per W row (d_out * element size)
     int64_t rows;
@@ -177,6 +185,11 @@ struct SlotRows {  // row n = (slot n / d_in, column c = n % d_in) of W_slot [d_
         return (const char *)w[sl] + c * es_dout;
     }
 };
+struct SlotList {
+    const void *p[kMaxSlots];
+    __device__ __forceinline__ const void *operator[](int64_t i) const { return p[i]; }
+};
+using SlotRows = SlotRowsOf<SlotList>;
 
 // K-contiguous rows whose element type is the LDS type.
 template <class TL, int NT, class RowPolicy>
@@ -320,13 +333,12 @@ struct LoadRowsHiLoBf16 {
     }
 };
 
-// fp32 weight side: 16 k x (ROWS / 4) chunks of 4 columns, transposed by scalar LDS writes
+// fp32 weight side: BK k x (ROWS / 4) chunks of 4 columns, transposed by scalar LDS writes
 // (used only in fp32 mode).
-template <int NT>
+template <class TL, int NT>
 struct LoadTransF32 {
-    using TL = TileF32;
-    static constexpr int NCH = 16 * (TL::ROWS / 4) / NT;
-    static_assert(NCH * NT == 16 * (TL::ROWS / 4), "threads must divide the tile's chunks");
+    static constexpr int NCH = TL::BK * (TL::ROWS / 4) / NT;
+    static_assert(NCH * NT == TL::BK * (TL::ROWS / 4), "threads must divide the tile's chunks");
     const char *base;
     int64_t ld_bytes;
     int64_t ksrc;
@@ -514,13 +526,14 @@ struct EpiDmsFwd {
 
 // dMs rows divided by the segment's degree.  The degrees a lane's epilogue needs are read
 // before the K loop (deg_of), so the epilogue waits for no load (store).
-struct EpiDms {
+template <class List>
+struct EpiDmsOf {
     static constexpr bool kPrefetch = true;
     float *out;
     int64_t M;
     int32_t N;
     int32_t d_in;
-    const int32_t *indptr[kMaxSlots];
+    List indptr;
     // degree of row m in the slot of column n; -1 where the slot has none (scale 1) or the
     // element is outside the output
     __device__ __forceinline__ int32_t deg_of(int64_t m, int64_t n) const {
@@ -548,6 +561,12 @@ struct EpiDms {
         }
     }
 };
+
+struct IndptrList {
+    const int32_t *p[kMaxSlots];
+    __device__ __forceinline__ const int32_t *operator[](int i) const { return p[i]; }
+};
+using EpiDms = EpiDmsOf<IndptrList>;
 
 struct EpiPartial {
     static constexpr bool kPrefetch = false;
@@ -577,20 +596,15 @@ struct EpiPartial {
 // R register stages: the global loads of step k + R are issued right after step k's tiles
 // reach LDS, so R multiplies overlap each load's latency.
 template <class C, class Mma, class LA, class LB, class Epi, int STAGES, int R>
-__global__ __launch_bounds__(C::NT) void k_gemm(const LA la, const LB lb, const Epi epi,
-                                                int64_t K, int64_t tiles_m, int64_t tiles_n,
-                                                int64_t k_per_split) {
+__device__ __forceinline__ void gemm_tile(const LA &la, const LB &lb, const Epi &epi, int64_t K,
+                                          int64_t tm, int64_t tn, int64_t split,
+                                          int64_t k_per_split) {
     using TL = typename Mma::T;
     constexpr int FM = C::FM, FN = C::FN;
     constexpr int STAGE_BYTES = Mma::STAGE_BYTES;
     constexpr int NW = C::NT / 64;
     __shared__ __attribute__((aligned(16))) char lds[STAGES * STAGE_BYTES];
     static_assert(STAGES * STAGE_BYTES >= NW * 16 * kStagePitch * 4, "epilogue staging space");
-    const int64_t logical = xcd_major_id(blockIdx.x, (int64_t)gridDim.x);
-    const int64_t tiles = tiles_m * tiles_n;
-    const int64_t split = logical / tiles;
-    const int64_t t = logical - split * tiles;
-    const int64_t tm = t / tiles_n, tn = t - tm * tiles_n;
     const int64_t m0 = tm * C::TM, n0 = tn * C::TN;
     const int64_t kb = split * k_per_split;
     const int64_t ke = kb + k_per_split < K ? kb + k_per_split : K;
@@ -715,6 +729,80 @@ __global__ __launch_bounds__(C::NT) void k_gemm(const LA la, const LB lb, const 
                             acc[mi][ni][8 * hh + e];
                 emit(m0 + wm * FM * 16 + mi * 32 + hh * 16, 2 * mi + hh);
             }
+        }
+    }
+}
+
+template <class C, class Mma, class LA, class LB, class Epi, int STAGES, int R>
+__global__ __launch_bounds__(C::NT) void k_gemm(const LA la, const LB lb, const Epi epi,
+                                                int64_t K, int64_t tiles_m, int64_t tiles_n,
+                                                int64_t k_per_split) {
+    const int64_t logical = xcd_major_id(blockIdx.x, (int64_t)gridDim.x);
+    const int64_t tiles = tiles_m * tiles_n;
+    const int64_t split = logical / tiles;
+    const int64_t t = logical - split * tiles;
+    const int64_t tm = t / tiles_n, tn = t - tm * tiles_n;
+    gemm_tile<C, Mma, LA, LB, Epi, STAGES, R>(la, lb, epi, K, tm, tn, split, k_per_split);
+}
+
+// The fp32 products of all types of a block in one launch (grid.y = type; workgroups past a
+// type's tiles leave at once).  Mode 0: forward; 1: input side; 2: weight side (split over
+// the rows).  The fp32 matrix rate sets the time of a tile (a 128 x 128 tile of K = 500
+// takes 27 us on its CU), so products of few tiles take 64 x 64 ones, which use four times
+// the CUs, and so do widths that fill them better (f32_small); K steps of 32.
+struct F32Tab {
+    struct Type {
+        const char *a, *b;        // A rows (mode 2: Mcat); B rows (mode 1: none; mode 2: dY)
+        float *out;               // y, dMs or the partial sums
+        const void *bias;
+        uint64_t *mask;
+        int64_t M, per;           // rows of the output (mode 2: rows reduced over, per split)
+        int32_t N, K, slot0, splits;   // mode 2: N = d_out, K = Kcat
+    } type[kMaxTypes];
+    const void *w[kMaxSlots];          // mode 1: weights and segment offsets of the slots
+    const int32_t *indptr[kMaxSlots];
+};
+template <class T>
+struct ListRef {   // a part of a list in the kernel's arguments
+    const T *p;
+    __device__ __forceinline__ T operator[](int64_t i) const { return p[i]; }
+};
+template <class C, int MODE>
+__global__ __launch_bounds__(C::NT) void k_gemm_f32(const F32Tab tab, int relu, int d_in) {
+    using TL = TileF32<C>;
+    using Core = MmaF32<TL, C::FM, C::FN>;
+    const F32Tab::Type &ty = tab.type[blockIdx.y];
+    const int64_t rows = MODE == 2 ? (int64_t)ty.K : ty.M;
+    const int64_t tiles_m = cdiv(rows, C::TM), tiles_n = cdiv(ty.N, C::TN);
+    const int64_t tiles = tiles_m * tiles_n, nwg = tiles * ty.splits;
+    if ((int64_t)blockIdx.x >= nwg) return;
+    const int64_t logical = xcd_major_id(blockIdx.x, nwg);
+    const int64_t split = logical / tiles;
+    const int64_t t = logical - split * tiles;
+    const int64_t tm = t / tiles_n, tn = t - tm * tiles_n;
+    if constexpr (MODE == 2) {
+        LoadTransF32<TL, C::NT> la{ty.a, (int64_t)ty.K * 4, ty.M, ty.K};
+        LoadTransF32<TL, C::NT> lb{ty.b, (int64_t)ty.N * 4, ty.M, ty.N};
+        gemm_tile<C, Core, decltype(la), decltype(lb), EpiPartial, 2, 2>(
+            la, lb, EpiPartial{ty.out, ty.K, ty.N}, ty.M, tm, tn, split, ty.per);
+    } else {
+        LoadRows<TL, C::NT, PlainRows> la{PlainRows{ty.a, (int64_t)ty.K * 4, ty.M},
+                                          (int64_t)ty.K * 4};
+        if constexpr (MODE == 0) {
+            LoadRows<TL, C::NT, PlainRows> lb{PlainRows{ty.b, (int64_t)ty.K * 4, ty.N},
+                                              (int64_t)ty.K * 4};
+            const ReluMask rm{ty.mask, (int64_t)(ty.N + 63) / 64};
+            gemm_tile<C, Core, decltype(la), decltype(lb), EpiForward<false>, 2, 2>(
+                la, lb, EpiForward<false>{ty.out, ty.bias, ty.M, ty.N, relu, rm}, ty.K, tm, tn, 0,
+                ty.K);
+        } else {
+            using Rows = SlotRowsOf<ListRef<const void *>>;
+            using Epi = EpiDmsOf<ListRef<const int32_t *>>;
+            LoadRows<TL, C::NT, Rows> lb{Rows{{tab.w + ty.slot0}, d_in, ty.K * 4, ty.N},
+                                         (int64_t)ty.K * 4};
+            gemm_tile<C, Core, decltype(la), decltype(lb), Epi, 2, 2>(
+                la, lb, Epi{ty.out, ty.M, ty.N, d_in, {tab.indptr + ty.slot0}}, ty.K, tm, tn, 0,
+                ty.K);
         }
     }
 }
@@ -1117,12 +1205,30 @@ __device__ __forceinline__ void dw_raw_frag(const char *tile, int row0, int col,
 // HILO: dY rows come in the hi/lo form (d_out bf16 high parts, then d_out low parts): the
 // hi and lo tiles are loaded like the Mcat tile and read by the same transpose reads, with
 // no split in registers.
+// The products of all types of a block in one launch, each type a range of the workgroups
+// (starting at a multiple of 8, which keeps the XCD mapping of a launch of its own).
+struct DwTab {
+    int32_t ntypes;
+    struct Type {
+        const char *mcat;
+        const float *dy;
+        float *partial;      // [splits][Kcat][d_out]
+        int64_t M, per;
+        int32_t Kcat, tiles_m, wg0, nwg;
+    } type[kMaxTypes];
+};
 template <class C, int BK, int S, int MINW, bool HILO>
-__global__ __launch_bounds__(C::NT, MINW) void k_gemm_dw(const char *__restrict__ mcat, int64_t M,
-                                                    int64_t Kcat, const float *__restrict__ dy,
-                                                    int64_t d_out, int64_t tiles_m,
-                                                    int64_t tiles_n, int64_t per,
-                                                    const EpiPartial epi) {
+__global__ __launch_bounds__(C::NT, MINW) void k_gemm_dw(const DwTab tab, int64_t d_out,
+                                                    int64_t tiles_n) {
+    int ty = 0;
+    for (int i = 1; i < tab.ntypes; ++i) ty = tab.type[i].wg0 <= (int)blockIdx.x ? i : ty;
+    const int bid = (int)blockIdx.x - tab.type[ty].wg0, nwg = tab.type[ty].nwg;
+    if (bid >= nwg) return;   // the padding before the next type's range
+    const char *__restrict__ mcat = tab.type[ty].mcat;
+    const float *__restrict__ dy = tab.type[ty].dy;
+    const int64_t M = tab.type[ty].M, Kcat = tab.type[ty].Kcat, per = tab.type[ty].per;
+    const int64_t tiles_m = tab.type[ty].tiles_m;
+    const EpiPartial epi{tab.type[ty].partial, Kcat, (int32_t)d_out};
     using Ga = DwGeom<BK, C::TM>;
     using Gb = DwRawGeom<BK, C::TN>;
     using Gh = DwGeom<BK, C::TN>;                  // HILO: each of the hi and lo tiles
@@ -1138,7 +1244,7 @@ __global__ __launch_bounds__(C::NT, MINW) void k_gemm_dw(const char *__restrict_
     __shared__ __attribute__((aligned(1024))) char lds[S * STAGE];
     static_assert(S * STAGE >= NW * 16 * kStagePitch * 4, "epilogue staging space");
 
-    const int64_t logical = xcd_major_id(blockIdx.x, (int64_t)gridDim.x);
+    const int64_t logical = xcd_major_id(bid, nwg);
     const int64_t tiles = tiles_m * tiles_n;
     const int64_t split = logical / tiles;
     const int64_t t = logical - split * tiles;
@@ -1455,6 +1561,49 @@ hipError_t launch_gemm(const LA &la, const LB &lb, const Epi &epi, int64_t M, in
     return hipGetLastError();
 }
 
+// compute units of the current device (cached per device)
+int64_t device_cus() {
+    static int64_t cache[64] = {0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (cache[dev] == 0) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            cus <= 0)
+            cus = 256;
+        cache[dev] = cus;
+    }
+    return cache[dev];
+}
+// Whether an fp32 launch takes 64 x 64 tiles: `tiles` = its 128 x 128 tiles, fewer than two
+// per CU, or N columns that 128-wide tiles pad by a quarter more than 64-wide ones.
+inline bool f32_small(int64_t tiles, int64_t N) {
+    return tiles < 2 * device_cus() || cdiv(N, 128) * 128 * 4 > cdiv(N, 64) * 64 * 5;
+}
+template <class C, int MODE>
+hipError_t launch_f32_as(const F32Tab &tab, int ntypes, int relu, int d_in, hipStream_t s) {
+    int64_t most = 0;
+    for (int t = 0; t < ntypes; ++t) {
+        const auto &ty = tab.type[t];
+        const int64_t n = cdiv(MODE == 2 ? (int64_t)ty.K : ty.M, C::TM) * cdiv(ty.N, C::TN) * ty.splits;
+        most = n > most ? n : most;
+    }
+    if (most == 0) return hipSuccess;
+    hipLaunchKernelGGL((k_gemm_f32<C, MODE>), dim3((unsigned)most, (unsigned)ntypes), dim3(C::NT), 0,
+                       s, tab, relu, d_in);
+    return hipGetLastError();
+}
+template <int MODE>
+hipError_t launch_f32(const F32Tab &tab, int ntypes, int relu, int d_in, hipStream_t s) {
+    int64_t tiles = 0, N = 0;
+    for (int t = 0; t < ntypes; ++t) {
+        tiles += cdiv(tab.type[t].M, CfgF32::TM) * cdiv(tab.type[t].N, CfgF32::TN);
+        N = tab.type[t].N > N ? tab.type[t].N : N;
+    }
+    return f32_small(tiles, N) ? launch_f32_as<CfgF32Small, MODE>(tab, ntypes, relu, d_in, s)
+                               : launch_f32_as<CfgF32, MODE>(tab, ntypes, relu, d_in, s);
+}
+
 // Split of the weight-side reduction over rows: at most `target` workgroups in total (one
 // wave of them where a workgroup fills a CU, so no partial second wave trails), each split
 // a whole number of K steps and at least 8 of them.
@@ -1472,26 +1621,46 @@ void dw_split(int64_t M, int Kcat, int d_out, int bk, int64_t target, int64_t *s
     *splits = M > 0 ? cdiv(M, p) : 0;
 }
 
-// dW_slot[c][o] = sum over splits (in order) of partial[split][slot * d_in + c][o]
-__global__ __launch_bounds__(kThreads) void k_dw_reduce(const float *partial, int64_t splits,
-                                                        int Kcat, int d_in, int d_out, DwOut out) {
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int64_t total = (int64_t)Kcat * d_out;
+// dW_slot[c][o] = sum over splits (in order) of partial[split][slot * d_in + c][o], all types
+// of a block in one launch; a type without splits (no rows) gets zeros.  V columns per
+// thread (4 where every output is 16-byte aligned), eight splits' loads in flight: one
+// column per thread and one load at a time took 26 us for 18 MB of partials.
+struct DwReduceTab {
+    int32_t ntypes;
+    struct Type {
+        const float *partial;
+        int64_t total;            // Kcat * d_out
+        int32_t splits, slot0, blk0;
+    } type[kMaxTypes];
+    float *w[kMaxSlots];
+};
+template <int V>
+__global__ __launch_bounds__(kThreads) void k_dw_reduce(DwReduceTab tab, int d_in, int d_out) {
+    typedef float vec __attribute__((ext_vector_type(V)));
+    int t = 0;
+    for (int i = 1; i < tab.ntypes; ++i) t = tab.type[i].blk0 <= (int)blockIdx.x ? i : t;
+    const int64_t total = tab.type[t].total;
+    const int64_t e = (((int64_t)blockIdx.x - tab.type[t].blk0) * kThreads + threadIdx.x) * V;
     if (e >= total) return;
-    const int64_t row = e / d_out, o = e - row * d_out;
+    const int64_t row = e / d_out, o = e - row * d_out;   // V divides d_out: one row
     const int sl = (int)(row / d_in);
-    float *dst = out.w[sl];
+    float *dst = tab.w[tab.type[t].slot0 + sl];
     if (!dst) return;
-    float acc = 0.f;
-    for (int64_t sp = 0; sp < splits; ++sp) acc += partial[sp * total + e];
-    dst[(row - (int64_t)sl * d_in) * d_out + o] = acc;
-}
-
-__global__ __launch_bounds__(kThreads) void k_zero_outputs(DwOut out, int d_in, int d_out) {
-    const int64_t per = (int64_t)d_in * d_out;
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    const int sl = (int)blockIdx.y;
-    if (e < per && out.w[sl]) out.w[sl][e] = 0.f;
+    const float *p = tab.type[t].partial + e;
+    const int splits = tab.type[t].splits;
+    vec acc;
+#pragma unroll
+    for (int q = 0; q < V; ++q) acc[q] = 0.f;
+    int sp = 0;
+    for (; sp + 8 <= splits; sp += 8) {
+        vec v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *(const vec *)(p + (int64_t)(sp + u) * total);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; sp < splits; ++sp) acc += *(const vec *)(p + (int64_t)sp * total);
+    *(vec *)(dst + (row - (int64_t)sl * d_in) * d_out + o) = acc;
 }
 
 // The input side's weight rows stacked as one bf16 [N x d_out] matrix (row s d_in + c =
@@ -1512,20 +1681,8 @@ constexpr int kDwStages = 2;   // LDS stages of k_gemm_dw (three measured 2 % sl
 // few workgroups); the fp32 kernel fits two per CU
 constexpr int64_t kDwTargetBf16 = 256;
 constexpr int64_t kDwTargetF32 = 512;
-// compute units of the current device (cached per device)
-int64_t device_cus() {
-    static int64_t cache[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (cache[dev] == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-        cache[dev] = cus;
-    }
-    return cache[dev];
-}
+constexpr int64_t kDwMinSteps = 4;   // shortest split, in K steps (2 and 8 measured the same)
+
 // forward transform: K step (elements) and LDS stages of k_gemm_fwd
 constexpr int kFwdBK = 64;
 constexpr int kFwdStages = 2;
@@ -1534,18 +1691,6 @@ constexpr int kDmsStages = 1;
 constexpr int kDmsRegStages = 1;
 
 }  // namespace
-
-static hipError_t gemm_forward_f32(const FwdGemm &g, int N, int relu, hipStream_t s) {
-    using C = CfgF32;
-    using TL = TileF32;
-    LoadRows<TL, C::NT, PlainRows> la{PlainRows{(const char *)g.a, (int64_t)g.K * 4, g.M},
-                                      (int64_t)g.K * 4};
-    LoadRows<TL, C::NT, PlainRows> lb{PlainRows{(const char *)g.wcat_t, (int64_t)g.K * 4, N},
-                                      (int64_t)g.K * 4};
-    const ReluMask rm{g.mask, (int64_t)(N + 63) / 64};
-    return launch_gemm<C, MmaF32<C::FM, C::FN>, decltype(la), decltype(lb), EpiForward<false>, 2, 2>(
-        la, lb, EpiForward<false>{g.y, g.bias, g.M, N, relu, rm}, g.M, N, g.K, 1, g.K, s);
-}
 
 // Workgroups of each type in a grouped launch of k_gemm_fwd, in groups of 8 (one per XCD):
 // a workgroup per tile where the tiles of all types fit the device; otherwise the device's
@@ -1617,9 +1762,11 @@ hipError_t gemm_forward(rgcn_dtype dt, const FwdGemm *g, int ntypes, int N, int 
                            dim3(C::NT), 0, s, tab);
         return hipGetLastError();
     }
+    F32Tab tab;
     for (int t = 0; t < ntypes; ++t)
-        RGCN_HIP_TRY(gemm_forward_f32(g[t], N, relu, s));
-    return hipSuccess;
+        tab.type[t] = {(const char *)g[t].a, (const char *)g[t].wcat_t, (float *)g[t].y, g[t].bias,
+                       g[t].mask, g[t].M, 0, N, g[t].K, 0, 1};
+    return launch_f32<0>(tab, ntypes, relu, 0, s);
 }
 
 hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int d_out,
@@ -1627,7 +1774,7 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
     const int es = dt == RGCN_BF16 ? 2 : 4;
     const int64_t N = (int64_t)slots.count * d_in;
     SlotRows sr;
-    for (int i = 0; i < kMaxSlots; ++i) sr.w[i] = i < slots.count ? slots.w[i] : nullptr;
+    for (int i = 0; i < kMaxSlots; ++i) sr.w.p[i] = i < slots.count ? slots.w[i] : nullptr;
     sr.d_in = d_in;
     sr.es_dout = d_out * es;
     sr.rows = N;
@@ -1667,15 +1814,15 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
     epi.M = M;
     epi.N = (int32_t)N;
     epi.d_in = d_in;
-    for (int i = 0; i < kMaxSlots; ++i) epi.indptr[i] = i < slots.count ? slots.indptr[i] : nullptr;
+    for (int i = 0; i < kMaxSlots; ++i) epi.indptr.p[i] = i < slots.count ? slots.indptr[i] : nullptr;
     PlainRows pa{(const char *)dy, (int64_t)d_out * 4, M};
     if (dt == RGCN_BF16 && N <= kDmsStreamCols && d_in % 16 == 0 &&
         (d_out == 256 || d_out == 512)) {
         if (M == 0) return hipSuccess;
         DmsStream ps{};
         for (int i = 0; i < kMaxSlots; ++i) {
-            ps.w[i] = sr.w[i];
-            ps.indptr[i] = epi.indptr[i];
+            ps.w[i] = sr.w.p[i];
+            ps.indptr[i] = epi.indptr.p[i];
         }
         ps.out = dms;
         ps.N = (int32_t)N;
@@ -1717,61 +1864,154 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
         return launch_gemm<C, Core, decltype(la), decltype(lb), EpiDms, kDmsStages,
                            kDmsRegStages>(la, lb, epi, M, N, d_out, 1, d_out, s);
     }
-    using C = CfgF32;
-    using TL = TileF32;
-    LoadRows<TL, C::NT, PlainRows> la{pa, (int64_t)d_out * 4};
-    LoadRows<TL, C::NT, SlotRows> lb{sr, (int64_t)d_out * 4};
-    return launch_gemm<C, MmaF32<C::FM, C::FN>, decltype(la), decltype(lb), EpiDms, 2, 2>(
-        la, lb, epi, M, N, d_out, 1, d_out, s);
+    return hipErrorInvalidValue;   // fp32: gemm_dms_f32
+}
+
+hipError_t gemm_dms_f32(const DmsGemm *g, int ntypes, int d_out, int d_in, const void *const *w,
+                        const int32_t *const *indptr, hipStream_t s) {
+    F32Tab tab;
+    int slots = 0;
+    for (int t = 0; t < ntypes; ++t) {
+        tab.type[t] = {(const char *)g[t].dy, nullptr, g[t].dms, nullptr, nullptr, g[t].M, 0,
+                       g[t].count * d_in, d_out, g[t].slot0, 1};
+        slots = g[t].slot0 + g[t].count > slots ? g[t].slot0 + g[t].count : slots;
+    }
+    for (int i = 0; i < kMaxSlots; ++i) {
+        tab.w[i] = i < slots ? w[i] : nullptr;
+        tab.indptr[i] = i < slots ? indptr[i] : nullptr;
+    }
+    return launch_f32<1>(tab, ntypes, 0, d_in, s);
 }
 
 size_t gemm_dw_partial_bytes(int64_t M, int Kcat, int d_out) {
+    // what every workspace holds for one type's partial sums: 128 x 128 fp32 tiles with
+    // splits of at least 128 rows, or the bf16 tiles
     int64_t sp16, p16, sp64, p64;
-    dw_split<CfgF32>(M, Kcat, d_out, TileF32::BK, kDwTargetF32, &sp16, &p16);
+    dw_split<CfgF32>(M, Kcat, d_out, 16, kDwTargetF32, &sp16, &p16);
     dw_split<CfgDw>(M, Kcat, d_out, kDwBK, kDwTargetBf16, &sp64, &p64);
     const int64_t sp = sp16 > sp64 ? sp16 : sp64;
     return (size_t)(sp > 0 ? sp : 1) * Kcat * d_out * 4 + 256;
 }
 
-hipError_t gemm_dw(rgcn_dtype dt, const void *mcat, int64_t M, int Kcat, int d_in,
-                   const float *dy, bool dy_hilo, int d_out, const DwOut &out, float *partial,
-                   hipStream_t s) {
-    const bool bf = dt == RGCN_BF16;
-    int64_t splits, per;
-    if (bf)
-        dw_split<CfgDw>(M, Kcat, d_out, kDwBK, kDwTargetBf16, &splits, &per);
-    else
-        dw_split<CfgF32>(M, Kcat, d_out, TileF32::BK, kDwTargetF32, &splits, &per);
-    if (splits == 0) {  // no rows: every requested gradient is zero
-        hipLaunchKernelGGL(k_zero_outputs, dim3((unsigned)cdiv((int64_t)d_in * d_out, kThreads),
-                           (unsigned)out.count), dim3(kThreads), 0, s, out, d_in, d_out);
-        return hipGetLastError();
+// Splits of all types together: one row count per split, the smallest (from an equal share
+// of the target workgroups up) at which the workgroups of all types, each type's range
+// padded to a multiple of 8, are at most `target` and the partial sums fit `room`.  False
+// where even whole reductions (one split each) do not fit.
+template <class C>
+bool dw_splits(const DwGemm *g, int n, int d_out, int bk, int64_t target, size_t room,
+               int64_t *splits, int64_t *per, size_t *want) {
+    const int64_t tiles_n = cdiv(d_out, C::TN);
+    double work = 0.;
+    int64_t longest = 0;
+    for (int t = 0; t < n; ++t) {
+        work += (double)g[t].M * (double)(cdiv(g[t].Kcat, C::TM) * tiles_n);
+        longest = g[t].M > longest ? g[t].M : longest;
     }
-    EpiPartial epi{partial, Kcat, d_out};
-    if (bf) {
+    int64_t len = cdiv((int64_t)(work / (double)target) + 1, bk) * bk;
+    if (len < kDwMinSteps * bk) len = kDwMinSteps * bk;
+    while (true) {
+        int64_t wgs = 0;
+        size_t bytes = 0;
+        for (int t = 0; t < n; ++t) {
+            splits[t] = cdiv(g[t].M, len);
+            // equal splits of whole steps
+            per[t] = splits[t] > 0 ? cdiv(cdiv(g[t].M, splits[t]), bk) * bk : bk;
+            if (splits[t] > 0) splits[t] = cdiv(g[t].M, per[t]);
+            wgs += cdiv(cdiv(g[t].Kcat, C::TM) * tiles_n * splits[t], 8) * 8;
+            bytes += ((size_t)splits[t] * g[t].Kcat * d_out * 4 + 255) / 256 * 256;
+        }
+        *want = bytes;
+        if (wgs <= target && bytes <= room) return true;
+        if (len >= longest) return bytes <= room;
+        len = cdiv(len + len / 256 + 1, bk) * bk;
+    }
+}
+
+static bool dw_plan(rgcn_dtype dt, const DwGemm *g, int n, int d_out, size_t room, int64_t *splits,
+                    int64_t *per, size_t *want) {
+    if (dt == RGCN_BF16)
+        return dw_splits<CfgDw>(g, n, d_out, kDwBK, kDwTargetBf16, room, splits, per, want);
+    return dw_splits<CfgF32Small>(g, n, d_out, kF32BK, kDwTargetF32, room, splits, per, want);
+}
+
+size_t gemm_dw_room(rgcn_dtype dt, const DwGemm *g, int ntypes, int d_out) {
+    int64_t splits[kMaxTypes], per[kMaxTypes];
+    size_t want = 0;
+    dw_plan(dt, g, ntypes, d_out, SIZE_MAX, splits, per, &want);
+    return want;
+}
+
+hipError_t gemm_dw(rgcn_dtype dt, const DwGemm *g, int ntypes, float *const *w, int d_in,
+                   bool dy_hilo, int d_out, float *partial, size_t room, hipStream_t s) {
+    if (ntypes == 0) return hipSuccess;
+    const bool bf = dt == RGCN_BF16;
+    int64_t splits[kMaxTypes], per[kMaxTypes];
+    size_t want = 0;
+    if (!dw_plan(dt, g, ntypes, d_out, room, splits, per, &want)) {
+        // the partial sums of one type always fit
+        for (int t = 0; t < ntypes; ++t)
+            RGCN_HIP_TRY(gemm_dw(dt, g + t, 1, w, d_in, dy_hilo, d_out, partial, room, s));
+        return hipSuccess;
+    }
+    F32Tab ftab;
+    int nf = 0;
+    const int64_t tiles_n = cdiv(d_out, CfgDw::TN);
+    DwTab tab;
+    DwReduceTab red;
+    tab.ntypes = 0;
+    red.ntypes = 0;
+    char *at = (char *)partial;
+    int64_t wg = 0, blk = 0;
+    bool vec = true;
+    for (int i = 0; i < kMaxSlots; ++i) red.w[i] = nullptr;
+    for (int t = 0; t < ntypes; ++t)
+        for (int i = 0; i < g[t].count; ++i) {
+            red.w[g[t].slot0 + i] = w[g[t].slot0 + i];
+            vec = vec && ((uintptr_t)w[g[t].slot0 + i] & 15u) == 0;
+        }
+    for (int t = 0; t < ntypes; ++t) {
+        auto &r = red.type[red.ntypes++];
+        r.partial = (const float *)at;
+        r.total = (int64_t)g[t].Kcat * d_out;
+        r.splits = (int32_t)splits[t];
+        r.slot0 = g[t].slot0;
+        r.blk0 = (int32_t)blk;
+        blk += cdiv(r.total, kThreads * (vec ? 4 : 1));
+        if (splits[t] == 0) continue;
+        if (bf) {
+            auto &ty = tab.type[tab.ntypes++];
+            ty.mcat = (const char *)g[t].mcat;
+            ty.dy = g[t].dy;
+            ty.partial = (float *)at;
+            ty.M = g[t].M;
+            ty.per = per[t];
+            ty.Kcat = g[t].Kcat;
+            ty.tiles_m = (int32_t)cdiv(g[t].Kcat, CfgDw::TM);
+            ty.wg0 = (int32_t)wg;
+            ty.nwg = (int32_t)(ty.tiles_m * tiles_n * splits[t]);
+            wg += cdiv(ty.nwg, 8) * 8;
+        } else {
+            ftab.type[nf++] = {(const char *)g[t].mcat, (const char *)g[t].dy, (float *)at, nullptr,
+                               nullptr, g[t].M, per[t], d_out, g[t].Kcat, 0, (int32_t)splits[t]};
+        }
+        at += ((size_t)splits[t] * g[t].Kcat * d_out * 4 + 255) / 256 * 256;
+    }
+    if (nf > 0) RGCN_HIP_TRY((launch_f32_as<CfgF32Small, 2>(ftab, nf, 0, 0, s)));
+    if (tab.ntypes > 0) {
         using C = CfgDw;
-        const int64_t tiles_m = cdiv(Kcat, C::TM), tiles_n = cdiv(d_out, C::TN);
         if (dy_hilo)
-            hipLaunchKernelGGL((k_gemm_dw<C, kDwBK, kDwStages, kDwMinWaves, true>),
-                               dim3((unsigned)(tiles_m * tiles_n * splits)),
-                               dim3(C::NT), 0, s, (const char *)mcat, M, (int64_t)Kcat, dy,
-                               (int64_t)d_out, tiles_m, tiles_n, per, epi);
+            hipLaunchKernelGGL((k_gemm_dw<C, kDwBK, kDwStages, kDwMinWaves, true>), dim3((unsigned)wg),
+                               dim3(C::NT), 0, s, tab, (int64_t)d_out, tiles_n);
         else
             hipLaunchKernelGGL((k_gemm_dw<C, kDwBK, kDwStages, kDwMinWaves, false>),
-                               dim3((unsigned)(tiles_m * tiles_n * splits)),
-                               dim3(C::NT), 0, s, (const char *)mcat, M, (int64_t)Kcat, dy,
-                               (int64_t)d_out, tiles_m, tiles_n, per, epi);
+                               dim3((unsigned)wg), dim3(C::NT), 0, s, tab, (int64_t)d_out, tiles_n);
         RGCN_HIP_TRY(hipGetLastError());
-    } else {
-        using C = CfgF32;
-        LoadTransF32<C::NT> la{(const char *)mcat, (int64_t)Kcat * 4, M, Kcat};
-        LoadTransF32<C::NT> lb{(const char *)dy, (int64_t)d_out * 4, M, d_out};
-        RGCN_HIP_TRY((launch_gemm<C, MmaF32<C::FM, C::FN>, decltype(la), decltype(lb), EpiPartial,
-                                  2, 2>(la, lb, epi, Kcat, d_out, M, splits, per, s)));
     }
-    const int64_t total = (int64_t)Kcat * d_out;
-    hipLaunchKernelGGL(k_dw_reduce, dim3((unsigned)cdiv(total, kThreads)), dim3(kThreads), 0, s,
-                       partial, splits, Kcat, d_in, d_out, out);
+    if (blk == 0) return hipSuccess;
+    if (vec)
+        hipLaunchKernelGGL(k_dw_reduce<4>, dim3((unsigned)blk), dim3(kThreads), 0, s, red, d_in, d_out);
+    else
+        hipLaunchKernelGGL(k_dw_reduce<1>, dim3((unsigned)blk), dim3(kThreads), 0, s, red, d_in, d_out);
     return hipGetLastError();
 }
 

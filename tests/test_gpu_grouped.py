@@ -1,0 +1,64 @@
+"""The dense products of all types in one launch: types of very different row counts (none
+among them) and K, widths that fill no tile, enough tiles for the large fp32 tiles, sign bits
+and biases; weight-gradient outputs that are not 16-byte aligned; a workspace without the
+room for all types' partial sums.  Against the oracle at the harness's bars."""
+import numpy as np
+import pytest
+import torch
+
+from harness import BlockRun, rel_err, to64, TOL
+from paper_2406_06022_amd import rgcn, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _block(seed, n_src, n_dst, rels, max_deg=4):
+    return synth.random_block(np.random.default_rng(seed), n_src, n_dst, rels, max_deg)
+
+
+MANY = ([900, 40, 70, 300, 65, 31], [700, 3, 0, 129, 64, 1],
+        [(0, 0), (1, 0), (3, 0), (0, 1), (2, 3), (0, 3), (3, 3), (5, 3), (4, 4), (0, 5), (1, 2)])
+
+
+@pytest.mark.parametrize("dtype,d_in,d_out,blk,relu", [
+    ("f32", 36, 100, MANY, True),
+    ("f32", 260, 64, MANY, False),
+    ("bf16", 72, 136, MANY, True),
+    ("bf16", 264, 520, MANY, False),
+    ("f32", 32, 256, ([40_000, 50], [38_500, 50], [(1, 0)]), False),   # 128 x 128 fp32 tiles
+    ("bf16", 64, 256, ([70_000, 300], [66_000, 300], [(1, 0), (0, 1)]), True),  # more tiles than CUs
+])
+def test_types_in_one_launch(dtype, d_in, d_out, blk, relu):
+    run = BlockRun(_block(d_in + d_out, *blk), dtype, d_in, d_out, seed=d_in, bias=True,
+                   fwd_relu=relu, mask_out=relu)
+    print(f"case grouped {dtype} {d_in}->{d_out} n_dst={blk[1]}", flush=True)
+    run.run_gpu()
+    run.run_oracle()
+    run.assert_parity()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_unaligned_gradients_and_small_workspace(dtype):
+    d_in, d_out = 72, 136
+    run = BlockRun(_block(7, *MANY), dtype, d_in, d_out, seed=3)
+    run.run_gpu()
+    run.run_oracle()
+    T, R = len(run.blk.n_src), len(run.blk.rels)
+    n = d_in * d_out
+    buf = torch.full((T + R, n + 1), float("nan"), device="cuda")   # rows at odd 4-byte offsets
+    dws = [buf[t, 1:].view(d_in, d_out) for t in range(T)]
+    dwr = [buf[T + r, 1:].view(d_in, d_out) for r in range(R)]
+    dy = [x.cuda() for x in run.dy]
+    # the same stages again on a workspace 256 bytes short of the reported size
+    ws = torch.full((run.ws.numel() - 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = [torch.empty((k, d_out), dtype=synth.torch_dtype(dtype), device="cuda") if k else None
+         for k in run.blk.n_dst]
+    rgcn.rgcn_block_plan(run.dblk, run.params, ws)
+    rgcn.rgcn_block_forward(run.dblk, run.inputs, run.params, y, ws)
+    rgcn.rgcn_block_backward(run.dblk, run.inputs, run.params, dy, dwr, dws, None, None, None, ws)
+    torch.cuda.synchronize()
+    for t in range(T):
+        assert rel_err(to64(dws[t]), run.ref["dw_self"][t]) <= TOL[dtype], t
+    for r in range(R):
+        assert rel_err(to64(dwr[r]), run.ref["dw_rel"][r]) <= TOL[dtype], r
+    assert bool(torch.isnan(buf[:, 0]).all())   # nothing written before a row
