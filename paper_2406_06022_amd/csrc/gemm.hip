@@ -56,6 +56,7 @@ struct Cfg {
 using CfgWide = Cfg<256, 256, 2, 4>;
 using CfgNarrow = Cfg<128, 128, 2, 2>;
 using CfgFwd = Cfg<256, 256, 4, 4>;   // bf16 forward: 16 waves of 64 x 64
+using CfgFwdSmall = Cfg<128, 128, 2, 2>;   // the same waves, for products of few tiles
 using CfgDms = CfgNarrow;   // bf16 input side: N is one or two slots of d_in columns
 // bf16 weight side (k_gemm_dw): 256 x 256 tiles of 8 waves, one workgroup per CU (16
 // waves of 64 x 64 measured 1 % slower)
@@ -1694,11 +1695,11 @@ constexpr int kDmsRegStages = 1;
 
 // Workgroups of each type in a grouped launch of k_gemm_fwd, in groups of 8 (one per XCD):
 // a workgroup per tile where the tiles of all types fit the device; otherwise the device's
-// workgroups (one per CU) handed out one group at a time to the type whose workgroups have
+// workgroups (per_cu on each CU) handed out one group at a time to the type whose workgroups have
 // the most left to do (tiles each, times the steps and the epilogue of a tile).
 template <class Tab>
-int64_t fwd_shares(Tab &tab, int bk) {
-    int64_t groups = device_cus() / 8, used = 0, need = 0;
+int64_t fwd_shares(Tab &tab, int bk, int per_cu) {
+    int64_t groups = device_cus() * per_cu / 8, used = 0, need = 0;
     if (groups < 1) groups = 1;
     int64_t tiles[kMaxTypes], cap[kMaxTypes], share[kMaxTypes];
     for (int t = 0; t < tab.ntypes; ++t) {
@@ -1736,10 +1737,33 @@ int64_t fwd_shares(Tab &tab, int bk) {
     return wg;
 }
 
+template <class C, class E>
+hipError_t launch_fwd_as(FwdTab<E> &tab, int per_cu, hipStream_t s) {
+    for (int t = 0; t < tab.ntypes; ++t) {
+        tab.type[t].tiles_m = (int32_t)cdiv(tab.type[t].M, C::TM);
+        tab.type[t].tiles_n = (int32_t)cdiv(tab.type[t].N, C::TN);
+    }
+    const int64_t P = fwd_shares(tab, kFwdBK, per_cu);
+    hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, E>), dim3((unsigned)P), dim3(C::NT), 0, s,
+                       tab);
+    return hipGetLastError();
+}
+template <class E>
+hipError_t launch_fwd(FwdTab<E> &tab, hipStream_t s) {
+    if (tab.ntypes == 0) return hipSuccess;
+    int64_t tiles = 0;
+    for (int t = 0; t < tab.ntypes; ++t)
+        tiles += cdiv(tab.type[t].M, CfgFwd::TM) * cdiv(tab.type[t].N, CfgFwd::TN);
+    // 128 x 128 tiles, two workgroups per CU, where the 256 x 256 ones leave a quarter of the
+    // CUs without a tile: 64 tiles of K = 10,752 took 245 us on 64 CUs, 155 us so; a two-layer
+    // inference of 40 tiles per block 142 -> 129 us.  The sums run in the same order.
+    return tiles * 4 <= device_cus() * 3 ? launch_fwd_as<CfgFwdSmall>(tab, 2, s)
+                                         : launch_fwd_as<CfgFwd>(tab, 1, s);
+}
+
 hipError_t gemm_forward(rgcn_dtype dt, const FwdGemm *g, int ntypes, int N, int relu,
                         hipStream_t s) {
     if (dt == RGCN_BF16) {
-        using C = CfgFwd;
         FwdTab<EpiForwardBf16> tab;
         tab.ntypes = 0;
         for (int t = 0; t < ntypes; ++t) {
@@ -1753,14 +1777,8 @@ hipError_t gemm_forward(rgcn_dtype dt, const FwdGemm *g, int ntypes, int N, int 
             ty.K = g[t].K;
             ty.epi = EpiForwardBf16{g[t].y, g[t].bias, g[t].M, N, relu,
                                     ReluMask{g[t].mask, (int64_t)(N + 63) / 64}};
-            ty.tiles_m = (int32_t)cdiv(g[t].M, C::TM);
-            ty.tiles_n = (int32_t)cdiv(N, C::TN);
         }
-        if (tab.ntypes == 0) return hipSuccess;
-        const int64_t P = fwd_shares(tab, kFwdBK);
-        hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, EpiForwardBf16>), dim3((unsigned)P),
-                           dim3(C::NT), 0, s, tab);
-        return hipGetLastError();
+        return launch_fwd(tab, s);
     }
     F32Tab tab;
     for (int t = 0; t < ntypes; ++t)
@@ -1780,9 +1798,7 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
     sr.rows = N;
     if (dt == RGCN_BF16 && dy_hilo && wpack != nullptr && d_in % 64 == 0 && N > kDmsStreamCols) {
         // the persistent product over the hi/lo rows (K = 2 d_out) and the packed weight rows
-        using C = CfgFwd;
-        const int64_t tiles_m = cdiv(M, C::TM), tiles_n = cdiv(N, C::TN);
-        if (tiles_m == 0) return hipSuccess;
+        if (M == 0) return hipSuccess;
         const int64_t chunks = N * (d_out / 8);
         const int64_t pb = cdiv(chunks, kThreads) < 4096 ? cdiv(chunks, kThreads) : 4096;
         hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)pb), dim3(kThreads), 0, s, sr, chunks,
@@ -1800,14 +1816,9 @@ hipError_t gemm_dms(rgcn_dtype dt, const float *dy, bool dy_hilo, int64_t M, int
         ty.K = (int64_t)d_out * 2;
         ty.epi = EpiDmsFwd{dms, M, (int32_t)N, d_out,
                            (uint32_t)(((1ull << 32) + (uint64_t)d_in - 1) / (uint64_t)d_in), 0};
-        ty.tiles_m = (int32_t)tiles_m;
-        ty.tiles_n = (int32_t)tiles_n;
         for (int i = 0; i < kMaxSlots; ++i)
             tab.indptr[i] = i < slots.count ? slots.indptr[i] : nullptr;
-        const int64_t P = fwd_shares(tab, kFwdBK);
-        hipLaunchKernelGGL((k_gemm_fwd<C, kFwdBK, kFwdStages, EpiDmsFwd>), dim3((unsigned)P),
-                           dim3(C::NT), 0, s, tab);
-        return hipGetLastError();
+        return launch_fwd(tab, s);
     }
     EpiDms epi;
     epi.out = dms;
