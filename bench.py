@@ -1014,7 +1014,7 @@ def measure_skewed(args, tables, dev):
            "ms_per_step": round(run["wall_ms"], 4), "step_ms_events": run["step_stats"],
            "edges_per_s": stack.nnz / (run["wall_ms"] / 1e3),
            "ms_per_block": block_ms(stack, avg),
-           "plan[0]": round(avg[("plan", 0)], 4), "plan_bwd[0]": round(avg[("plan_bwd", 0)], 4),
+           "plan[0]": round(avg[("plan", 0)], 4), "plan_bwd[0]": round(avg.get(("plan_bwd", 0), 0.0), 4),
            "sparse[0]": dict(roof["sparse[0]"], kernel="k_transpose_pipe"),
            "aggregate[0]": roof["aggregate[0]"],
            "largest_transpose_degree": longest, "sources_over_32_edges": hubs,

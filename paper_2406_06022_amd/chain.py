@@ -22,6 +22,12 @@ from . import rgcn
 
 
 class MiniBatchStack:
+    # Edges of a mini-batch from which step() overlaps the plans: below, the second stream's
+    # events and the plan's second set of calls cost more than the overlap hides (us per step,
+    # overlapped / serial: 0.17M edges 279 / 237, 1.1M 690 / 671, 7.7M 2,578 / 2,559, 46M
+    # 15,050 / 15,170).
+    overlap_min_edges = 1 << 24
+
     def __init__(self, blocks, input_tables: Sequence[Optional[torch.Tensor]],
                  input_ids: Sequence[Optional[torch.Tensor]], weights, dtype: str,
                  dims: Sequence[int], emb_types: Sequence[int] = (), device="cuda",
@@ -210,11 +216,12 @@ class MiniBatchStack:
     def step(self, dy_top, timer=None, overlap_plan: bool = True) -> None:
         """One pass of the whole path: plan, forward, backward.
 
-        With overlap_plan the plan is split: the forward part of every block runs first;
+        With overlap_plan, a mini-batch of at least overlap_min_edges edges splits the plan:
+        the forward part of every block runs first;
         the backward part (CSC transposes and backward schedules) runs on a second stream
         from the end of the first block's aggregate stage, next to the MFMA-bound transforms,
         and the backward waits for it.  Same work and results as the serial order."""
-        if not overlap_plan:
+        if not overlap_plan or self.nnz < self.overlap_min_edges:
             self.plan(timer=timer)
             self.forward(timer=timer)
             self.backward(dy_top, timer=timer)
