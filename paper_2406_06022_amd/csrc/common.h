@@ -391,6 +391,14 @@ size_t gemm_dw_room(rgcn_dtype dt, const DwGemm *g, int ntypes, int d_out);
 hipError_t gemm_dw(rgcn_dtype dt, const DwGemm *g, int ntypes, float *const *w, int d_in,
                    bool dy_hilo, int d_out, float *partial, size_t room, hipStream_t s);
 
+// fp32 products of the in-batch decoder, any sizes, 4-byte alignment:
+// c [M x N] = a [M x K] (b [N x K])^T;
+// du [M x N] = g [M x K] h [K x N] and, unless dh is NULL, dh [K x N] = g^T u [M x N].
+hipError_t f32_scores(const float *a, const float *b, float *c, int64_t M, int64_t N, int64_t K,
+                      hipStream_t s);
+hipError_t f32_score_grads(const float *g, const float *h, const float *u, float *du, float *dh,
+                           int64_t M, int64_t N, int64_t K, hipStream_t s);
+
 }  // namespace rgcn
 
 #define RGCN_HIP_TRY(expr)                         \

@@ -808,6 +808,142 @@ __global__ __launch_bounds__(C::NT) void k_gemm_f32(const F32Tab tab, int relu, 
     }
 }
 
+// fp32 products over plain matrices of any size and 4-byte alignment (the in-batch link
+// prediction decoder: B x B scores of odd B among them): the same tiles and cores, 16-byte
+// accesses that need only 4-byte alignment, row and column tails element by element.
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+__device__ __forceinline__ u32x4 load4_tail(const float *p, bool ok, int64_t left) {
+    const bool whole = ok && left >= 4;
+    f32x4 v = *(const f32x4u *)(whole ? p : (const float *)g_zero16);
+    if (ok && !whole)
+        for (int e = 0; e < 4; ++e)
+            if (e < left) v[e] = p[e];
+    return __builtin_bit_cast(u32x4, v);
+}
+template <class TL, int NT>
+struct LoadRowsU {
+    static constexpr int NCH = TL::ROWS * TL::CPR / NT;
+    const float *base;
+    int64_t ld, rows, K;
+    struct State {
+        int64_t row[NCH];
+        int lr[NCH], lq[NCH];
+        u32x4 reg[NCH];
+    };
+    __device__ __forceinline__ void init(State &st, int64_t row0) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int chunk = threadIdx.x + c * NT;
+            st.lr[c] = chunk / TL::CPR;
+            st.lq[c] = chunk % TL::CPR;
+            st.row[c] = row0 + st.lr[c];
+        }
+    }
+    __device__ __forceinline__ void load(State &st, int64_t k0, int64_t kend) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int64_t k = k0 + st.lq[c] * 4;
+            st.reg[c] = load4_tail(base + st.row[c] * ld + k, st.row[c] < rows && k < kend, kend - k);
+        }
+    }
+    __device__ __forceinline__ void store(const State &st, char *lds) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+            *(u32x4 *)(lds + st.lr[c] * TL::PITCH + st.lq[c] * 16) = st.reg[c];
+    }
+};
+template <class TL, int NT>
+struct LoadTransU {
+    static constexpr int NCH = TL::BK * (TL::ROWS / 4) / NT;
+    const float *base;
+    int64_t ld, cols, K;
+    struct State {
+        int64_t col0;
+        int ik[NCH], cq[NCH];
+        u32x4 reg[NCH];
+    };
+    __device__ __forceinline__ void init(State &st, int64_t c0) const {
+        st.col0 = c0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int chunk = threadIdx.x + c * NT;
+            st.ik[c] = chunk / (TL::ROWS / 4);
+            st.cq[c] = chunk % (TL::ROWS / 4);
+        }
+    }
+    __device__ __forceinline__ void load(State &st, int64_t k0, int64_t kend) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int64_t i = k0 + st.ik[c], col = st.col0 + (int64_t)st.cq[c] * 4;
+            st.reg[c] = load4_tail(base + i * ld + col, i < kend && col < cols, cols - col);
+        }
+    }
+    __device__ __forceinline__ void store(const State &st, char *lds) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const u32x4 v = st.reg[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *(uint32_t *)(lds + (st.cq[c] * 4 + e) * TL::PITCH + st.ik[c] * 4) = v[e];
+        }
+    }
+};
+struct EpiPlain {
+    static constexpr bool kPrefetch = false;
+    static constexpr bool kMask = false;
+    float *out;
+    int64_t M, N;
+    __device__ __forceinline__ void operator()(int64_t m, int64_t n0, const float *v, int64_t) const {
+        if (m >= M) return;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t n = n0 + 16 * q;
+            float *o = out + m * N + n;
+            if (n + 4 <= N) {
+                *(f32x4u *)o = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            } else {
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) o[e] = v[4 * q + e];
+            }
+        }
+    }
+};
+// GRAD false: c0 [M x N] = a0 b0^T, both K-contiguous rows.  GRAD true, blockIdx.y 0:
+// c0 [M x N] = a0 b0 (b0 [K x N]); 1: c1 [K x N] = a0^T b1 (b1 [M x N]).
+struct F32Prods {
+    const float *a0, *b0, *b1;
+    float *c0, *c1;
+    int64_t M, N, K;
+};
+template <bool GRAD>
+__global__ __launch_bounds__(CfgF32Small::NT) void k_prod_f32(const F32Prods p) {
+    using C = CfgF32Small;
+    using TL = TileF32<C>;
+    using Core = MmaF32<TL, C::FM, C::FN>;
+    using Rows = LoadRowsU<TL, C::NT>;
+    using Trans = LoadTransU<TL, C::NT>;
+    const bool second = GRAD && blockIdx.y == 1;
+    const int64_t rows = second ? p.K : p.M;
+    const int64_t tiles_n = cdiv(p.N, C::TN), tiles = cdiv(rows, C::TM) * tiles_n;
+    if ((int64_t)blockIdx.x >= tiles) return;
+    const int64_t t = xcd_major_id(blockIdx.x, tiles);
+    const int64_t tm = t / tiles_n, tn = t - tm * tiles_n;
+    if constexpr (!GRAD) {
+        gemm_tile<C, Core, Rows, Rows, EpiPlain, 2, 2>(Rows{p.a0, p.K, p.M, p.K},
+                                                       Rows{p.b0, p.K, p.N, p.K},
+                                                       EpiPlain{p.c0, p.M, p.N}, p.K, tm, tn, 0, p.K);
+    } else if (!second) {
+        gemm_tile<C, Core, Rows, Trans, EpiPlain, 2, 2>(Rows{p.a0, p.K, p.M, p.K},
+                                                        Trans{p.b0, p.N, p.N, p.K},
+                                                        EpiPlain{p.c0, p.M, p.N}, p.K, tm, tn, 0, p.K);
+    } else {
+        gemm_tile<C, Core, Trans, Trans, EpiPlain, 2, 2>(Trans{p.a0, p.K, p.K, p.M},
+                                                         Trans{p.b1, p.N, p.N, p.M},
+                                                         EpiPlain{p.c1, p.K, p.N}, p.M, tm, tn, 0,
+                                                         p.M);
+    }
+}
+
 // ------------------------------------------------------------------ direct-load kernel
 // bf16 products whose operands are both K-contiguous rows (the forward transform).  Tiles
 // go from global memory straight into LDS (16 bytes per lane per instruction, lane L's
@@ -2023,6 +2159,28 @@ hipError_t gemm_dw(rgcn_dtype dt, const DwGemm *g, int ntypes, float *const *w, 
         hipLaunchKernelGGL(k_dw_reduce<4>, dim3((unsigned)blk), dim3(kThreads), 0, s, red, d_in, d_out);
     else
         hipLaunchKernelGGL(k_dw_reduce<1>, dim3((unsigned)blk), dim3(kThreads), 0, s, red, d_in, d_out);
+    return hipGetLastError();
+}
+
+hipError_t f32_scores(const float *a, const float *b, float *c, int64_t M, int64_t N, int64_t K,
+                      hipStream_t s) {
+    if (M == 0 || N == 0) return hipSuccess;
+    const F32Prods p{a, b, nullptr, c, nullptr, M, N, K};
+    hipLaunchKernelGGL(k_prod_f32<false>,
+                       dim3((unsigned)(cdiv(M, CfgF32Small::TM) * cdiv(N, CfgF32Small::TN))),
+                       dim3(CfgF32Small::NT), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t f32_score_grads(const float *g, const float *h, const float *u, float *du, float *dh,
+                           int64_t M, int64_t N, int64_t K, hipStream_t s) {
+    if (M == 0 || N == 0 || K == 0) return hipSuccess;
+    const F32Prods p{g, h, u, du, dh, M, N, K};
+    const int64_t rows = dh != nullptr && K > M ? K : M;
+    hipLaunchKernelGGL(k_prod_f32<true>,
+                       dim3((unsigned)(cdiv(rows, CfgF32Small::TM) * cdiv(N, CfgF32Small::TN)),
+                            dh != nullptr ? 2u : 1u),
+                       dim3(CfgF32Small::NT), 0, s, p);
     return hipGetLastError();
 }
 

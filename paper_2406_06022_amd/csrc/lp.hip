@@ -5,15 +5,15 @@
 // contrastive loss averaged over the batch, and the gradients with respect to every
 // embedding row used (added into a table-shaped fp32 buffer) and to r.
 //
-// Passes: (1) scores, one lane group per positive with u_i = h_src_i * r held in
-// registers (u_i also stored for the later passes), negatives four at a time;
-// (2) the loss per positive and the derivative of the loss with respect to each score;
-// (3) a fixed-order sum of the per-positive losses; (4) per positive, the gradient of
-// u_i (gpos h_dst + sum_k G_ik h_neg), scattered into the source row (times r) and, per
-// edge, G_ik u_i into each negative row, plus gpos u_i into the destination row; the
-// products dU_i * h_src_i for the gradient of r; (5) for shared negatives (joint,
-// in-batch) the negative rows' gradients per column, sum_i G_ik u_i, one add per column;
-// (6) the column sums that give the gradient of r.
+// Passes: (1) scores: u_i = h_src_i * r (stored for the later passes) and, per edge, one
+// lane group per positive with its negatives four at a time; with shared negatives (joint,
+// in-batch) products of U and the negatives' rows; (2) the loss per positive and the
+// derivative of the loss with respect to each score; (3) with shared negatives the products
+// that give dU and the negative rows' gradients; (4) per positive, the gradient of u_i
+// scattered into the source row (times r), gpos u_i into the destination row, per edge G_ik
+// u_i into each negative row (shared negatives: one add per column), and the products
+// dU_i * h_src_i for the gradient of r; (5) the sums over positives: the loss and, from
+// column sums of those products, the gradient of r.
 //
 // Large per-edge batches take k_lp_edges and k_lp_rows instead: passes (1), (2) and dU_i in
 // one read of the negatives' rows, then the embedding gradient row by row over the edges
@@ -81,7 +81,7 @@ __device__ __forceinline__ int64_t neg_row(const LpArgs &a, int64_t i, int64_t k
 // lg + p G (p < CPL) of u_i.
 template <bool BF16, int CPL>
 __global__ __launch_bounds__(kThreads) void k_lp_scores(LpArgs a, int G, float *pos, float *S,
-                                                        float *U, int loop_negs) {
+                                                        float *U) {
     constexpr int VEC = Row<BF16>::VEC;
     const int lane = threadIdx.x & 63;
     const int lg = lane & (G - 1);
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(kThreads) void k_lp_scores(LpArgs a, int G, float *
             acc = group_sum(acc, G);
             if (lg == 0) pos[i] = acc;
         }
-        for (int64_t k0 = 0; loop_negs && k0 < a.nn; k0 += 4) {
+        for (int64_t k0 = 0; k0 < a.nn; k0 += 4) {
             float acc[4] = {0.f, 0.f, 0.f, 0.f};
             int64_t rows[4];
 #pragma unroll
@@ -157,8 +157,10 @@ __device__ __forceinline__ int64_t loss_col(bool full, int64_t i, int64_t k) {
     return full ? (k < i ? k : k + 1) : k;
 }
 
+// out (in-batch, or NULL): the caller's neg_score, S[i][k < i ? k : k + 1].
 __global__ __launch_bounds__(kThreads) void k_lp_loss(LpArgs a, const float *pos, const float *S,
-                                                      float *gpos, float *Gm, float *lossp) {
+                                                      float *gpos, float *Gm, float *lossp,
+                                                      float *out) {
     const int lane = threadIdx.x & 63;
     const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
     const double n_edges = (double)a.batch * (double)(1 + a.nn);
@@ -168,6 +170,8 @@ __global__ __launch_bounds__(kThreads) void k_lp_loss(LpArgs a, const float *pos
         const float sp = pos[i];
         const float *Si = S + i * ld;
         float *Gi = Gm + i * ld;
+        if (out != nullptr)
+            for (int64_t k = lane; k < a.nn; k += 64) out[i * a.nn + k] = Si[loss_col(full, i, k)];
         if (a.loss == RGCN_LP_CONTRASTIVE) {
             float m = sp;
             for (int64_t k = lane; k < a.nn; k += 64) m = fmaxf(m, Si[loss_col(full, i, k)]);
@@ -206,24 +210,13 @@ __global__ __launch_bounds__(kThreads) void k_lp_loss(LpArgs a, const float *pos
     }
 }
 
-// (3) the batch loss: one workgroup, fixed order (deterministic).
-__global__ __launch_bounds__(kThreads) void k_lp_sum(const float *lossp, int64_t n, float *out) {
-    __shared__ float buf[kThreads];
-    float acc = 0.f;
-    for (int64_t i = threadIdx.x; i < n; i += kThreads) acc += lossp[i];
-    buf[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = kThreads / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) buf[threadIdx.x] += buf[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = buf[0];
-}
-
 // Shared negatives as dense products, per group of positives (joint: K positives and
 // their K shared rows; in-batch: all B positives and the B destination rows):
 //   S_g = U_g Hn_g^T,  dU_g = G_g Hn_g,  dHn_g = G_g^T U_g.
-// A generic batched fp32 tile product C = A B^T over strided operands: 32 x 32 tiles, one
+// In-batch they are fp32 products on 64 x 64 tiles of four waves (f32_scores,
+// f32_score_grads, the two gradients in one launch): at B 1,024, d 512 the three took 156 us
+// as one wave per 32 x 32 tile, and 61 us so.
+// Joint: a generic batched fp32 tile product C = A B^T over strided operands: 32 x 32 tiles, one
 // wave each (a batch of 1,024 positives makes 1,024 tiles, four per CU), K steps of 16
 // through LDS, fp32 MFMA.  Rows of A (or the reduction, for dHn) that lie past the batch
 // in a group's last tile are left out.
@@ -300,20 +293,49 @@ __device__ __forceinline__ int64_t col_row(const LpArgs &a, int64_t c) {
     return a.neg_mode == RGCN_LP_NEG_JOINT ? a.neg[c] : a.dst[c];
 }
 
-// Hn[c] = emb[col_row(c)] in fp32.
+// Shared negatives, pass (1): u_i and the positive scores, and Hn[c] = emb[col_row(c)], all
+// in fp32; one wave per row (in-batch, a positive's destination row is also column i).
 template <bool BF16>
-__global__ __launch_bounds__(kThreads) void k_lp_gather(LpArgs a, int64_t ncols, float *Hn) {
-    const int64_t total = ncols * a.d;
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * kThreads) {
-        const int64_t c = t / a.d, e = t - c * a.d;
-        const int64_t row = col_row(a, c);
-        if constexpr (BF16) {
-            const uint16_t v = ((const uint16_t *)a.emb)[row * a.ld + e];
-            Hn[t] = __uint_as_float((uint32_t)v << 16);
-        } else {
-            Hn[t] = ((const float *)a.emb)[row * a.ld + e];
+__global__ __launch_bounds__(kThreads) void k_lp_shared_rows(LpArgs a, int64_t ncols, float *pos,
+                                                             float *U, float *Hn) {
+    constexpr int VEC = Row<BF16>::VEC;
+    const int lane = threadIdx.x & 63;
+    const bool inbatch = a.neg_mode == RGCN_LP_NEG_IN_BATCH;
+    const int chunks = a.d / VEC;
+    const int64_t items = a.batch + (inbatch ? 0 : ncols);
+    const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
+    auto put = [&](float *row, int c, const float (&v)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; e += 4)
+            *(float4 *)(row + c * VEC + e) = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+    };
+    for (int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6; i < items; i += waves) {
+        if (i >= a.batch) {
+            const int64_t col = i - a.batch, row = col_row(a, col);
+            for (int c = lane; c < chunks; c += 64) {
+                float h[VEC];
+                load_chunk<BF16>(a, row, c, h);
+                put(Hn + col * a.d, c, h);
+            }
+            continue;
         }
+        const int64_t sr = a.src[i], dr = a.dst[i];
+        float acc = 0.f;
+        for (int c = lane; c < chunks; c += 64) {
+            float h[VEC], r[VEC], v[VEC];
+            load_chunk<BF16>(a, sr, c, h);
+            load_chunk<BF16>(a, dr, c, v);
+            load_rel<BF16>(a, c, r);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                h[e] *= r[e];
+                acc += h[e] * v[e];
+            }
+            put(U + i * a.d, c, h);
+            if (inbatch) put(Hn + i * a.d, c, v);
+        }
+        acc = group_sum(acc, 64);
+        if (lane == 0) pos[i] = acc;
     }
 }
 
@@ -353,7 +375,7 @@ __device__ __forceinline__ float rel_elem(const LpArgs &a, int64_t e) {
 template <bool BF16, int J>
 __global__ __launch_bounds__(kThreads) void k_lp_finish(LpArgs a, const float *gpos, const float *Gm,
                                                         const float *U, const float *dU,
-                                                        float *d_emb, float *P) {
+                                                        const float *dHn, float *d_emb, float *P) {
     const int lane = threadIdx.x & 63;
     const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
     const bool per_edge = a.neg_mode == RGCN_LP_NEG_PER_EDGE;
@@ -377,6 +399,12 @@ __global__ __launch_bounds__(kThreads) void k_lp_finish(LpArgs a, const float *g
             for (int j = 0; j < J; ++j) {
                 const int64_t e = lane + 64 * j;
                 if (e < a.d) unsafeAtomicAdd(d_emb + dr * a.d + e, gp * u[j]);
+            }
+        if (dHn && d_emb)   // in-batch: column i's gradient, the positive's among it
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int64_t e = lane + 64 * j;
+                if (e < a.d) unsafeAtomicAdd(d_emb + dr * a.d + e, dHn[i * a.d + e]);
             }
         if (per_edge) {
             // Per chunk of 64 negatives, lane l loads negative l's row and weight once (the
@@ -436,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void k_lp_finish(LpArgs a, const float *g
     }
 }
 
-// (6) d_rel = sum_i P_i: a workgroup takes 64 columns of a slice of rows with 4 row
+// (5) d_rel = sum_i P_i: a workgroup takes 64 columns of a slice of rows with 4 row
 // lanes per column (coalesced 256-byte rows), the lanes combined in LDS; then the slices
 // of each column in order.
 constexpr int kRelCols = 64, kRelLanes = kThreads / kRelCols;
@@ -458,31 +486,11 @@ __global__ __launch_bounds__(kThreads) void k_lp_rel_partial(const float *P, int
         part[(int64_t)blockIdx.y * d + e] = t;
     }
 }
-__global__ __launch_bounds__(kThreads) void k_lp_rel_final(const float *part, int64_t nparts, int d,
-                                                           float *out) {
-    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= d) return;
-    float acc = 0.f;
-    for (int64_t p = 0; p < nparts; ++p) acc += part[p * d + e];
-    out[e] = acc;
-}
-
 // Row slices of the d_rel reduction: 64 rows each, at most 256 slices.
 int64_t rel_parts(int64_t rows) {
     int64_t p = cdiv(rows, 64);
     return p < 1 ? 1 : (p > 256 ? 256 : p);
 }
-
-// neg_score[i][k] = S[i][k < i ? k : k + 1] for the in-batch product.
-__global__ __launch_bounds__(kThreads) void k_lp_offdiag(const float *S, int64_t B, float *out) {
-    const int64_t total = B * (B - 1);
-    for (int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * kThreads) {
-        const int64_t i = t / (B - 1), k = t - i * (B - 1);
-        out[t] = S[i * B + (k < i ? k : k + 1)];
-    }
-}
-
 
 __global__ __launch_bounds__(kThreads) void k_lp_validate(LpArgs a, uint32_t *err) {
     const int64_t nneg = a.neg_mode == RGCN_LP_NEG_PER_EDGE ? a.batch * a.k
@@ -764,15 +772,17 @@ __global__ __launch_bounds__(kThreads, CPL == 1 ? 4 : 1) void k_lp_edges(
     }
 }
 
-// The workgroups' partial losses and relation gradients, each added in a fixed order:
+// Partial losses and partial relation gradients, each added in a fixed order:
 // workgroup 0 the loss, the others 8 columns of d_rel each with 32 lanes per column.
-__global__ __launch_bounds__(kThreads) void k_lp_edges_final(const float *part_loss,
-                                                             const float *part_rel, int n, int d,
-                                                             float *loss, float *d_rel) {
+__global__ __launch_bounds__(kThreads) void k_lp_final(const float *part_loss,
+                                                             const float *part_rel, int64_t nloss,
+                                                             int nrel, int d, float *loss,
+                                                             float *d_rel) {
     __shared__ float buf[kThreads];
     float acc = 0.f;
     if (blockIdx.x == 0) {
-        for (int i = threadIdx.x; i < n; i += kThreads) acc += part_loss[i];
+#pragma unroll 8
+        for (int64_t i = threadIdx.x; i < nloss; i += kThreads) acc += part_loss[i];
         buf[threadIdx.x] = acc;
         __syncthreads();
         for (int o = kThreads / 2; o > 0; o >>= 1) {
@@ -786,7 +796,7 @@ __global__ __launch_bounds__(kThreads) void k_lp_edges_final(const float *part_l
     const int e = ((int)blockIdx.x - 1) * kFinalCols + c;
     if (e < d)
 #pragma unroll 8
-        for (int i = l; i < n; i += kThreads / kFinalCols) acc += part_rel[(int64_t)i * d + e];
+        for (int i = l; i < nrel; i += kThreads / kFinalCols) acc += part_rel[(int64_t)i * d + e];
     buf[threadIdx.x] = acc;
     __syncthreads();
     for (int o = kThreads / 2; o >= kFinalCols; o >>= 1) {
@@ -966,33 +976,32 @@ int64_t grid_for(int64_t items, int per_wg) {
 }
 
 template <bool BF16, int CPL>
-hipError_t run_scores(const LpArgs &a, int G, float *pos, float *S, float *U, int loop_negs,
-                      hipStream_t s) {
+hipError_t run_scores(const LpArgs &a, int G, float *pos, float *S, float *U, hipStream_t s) {
     hipLaunchKernelGGL((k_lp_scores<BF16, CPL>), dim3((unsigned)grid_for(a.batch, kThreads / G)),
-                       dim3(kThreads), 0, s, a, G, pos, S, U, loop_negs);
+                       dim3(kThreads), 0, s, a, G, pos, S, U);
     return hipGetLastError();
 }
 
 template <bool BF16>
-hipError_t dispatch_scores(const LpArgs &a, float *pos, float *S, float *U, int loop_negs,
-                           hipStream_t s) {
+hipError_t dispatch_scores(const LpArgs &a, float *pos, float *S, float *U, hipStream_t s) {
     const int chunks = a.d / Row<BF16>::VEC;
     int G = 1;
     while (G < chunks && G < 64) G *= 2;
     const int cpl = (int)cdiv(chunks, G);
-    if (cpl == 1) return run_scores<BF16, 1>(a, G, pos, S, U, loop_negs, s);
-    if (cpl == 2) return run_scores<BF16, 2>(a, G, pos, S, U, loop_negs, s);
-    if (cpl <= 4) return run_scores<BF16, 4>(a, G, pos, S, U, loop_negs, s);
+    if (cpl == 1) return run_scores<BF16, 1>(a, G, pos, S, U, s);
+    if (cpl == 2) return run_scores<BF16, 2>(a, G, pos, S, U, s);
+    if (cpl <= 4) return run_scores<BF16, 4>(a, G, pos, S, U, s);
     return hipErrorInvalidValue;
 }
 
 template <bool BF16>
 hipError_t dispatch_finish(const LpArgs &a, const float *gpos, const float *Gm, const float *U,
-                           const float *dU, float *d_emb, float *P, hipStream_t s) {
+                           const float *dU, const float *dHn, float *d_emb, float *P,
+                           hipStream_t s) {
     const dim3 grid((unsigned)grid_for(a.batch, kThreads / 64)), block(kThreads);
     const int J = (int)cdiv(a.d, 64);
 #define RGCN_FIN(JJ) \
-    hipLaunchKernelGGL((k_lp_finish<BF16, JJ>), grid, block, 0, s, a, gpos, Gm, U, dU, d_emb, P)
+    hipLaunchKernelGGL((k_lp_finish<BF16, JJ>), grid, block, 0, s, a, gpos, Gm, U, dU, dHn, d_emb, P)
     if (J <= 1) RGCN_FIN(1);
     else if (J <= 2) RGCN_FIN(2);
     else if (J <= 4) RGCN_FIN(4);
@@ -1038,6 +1047,13 @@ EdgePlan edge_plan(const LpArgs &a, const LpLayout &L) {
     return e;
 }
 
+hipError_t final_sums(const LpArgs &a, const float *part_loss, int64_t nloss, const float *part_rel,
+                      int nrel, float *loss, float *d_rel, hipStream_t s) {
+    hipLaunchKernelGGL(k_lp_final, dim3((unsigned)(1 + (d_rel ? cdiv(a.d, kFinalCols) : 0))),
+                       dim3(kThreads), 0, s, part_loss, part_rel, nloss, nrel, a.d, loss, d_rel);
+    return hipGetLastError();
+}
+
 template <bool BF16, int CPL>
 hipError_t run_edges(const LpArgs &a, const EdgePlan &e, char *ws, float *pos, float *S,
                      float *gpos, float *d_emb, float *d_rel, hipStream_t s) {
@@ -1079,10 +1095,8 @@ hipError_t lp_edges(const LpArgs &a, const EdgePlan &e, char *ws, float *loss, f
     else if (e.cpl <= 4) { if (bf) RGCN_EDGES(true, 4); else RGCN_EDGES(false, 4); }
     else return hipErrorInvalidValue;
 #undef RGCN_EDGES
-    hipLaunchKernelGGL(k_lp_edges_final, dim3((unsigned)(1 + (d_rel ? cdiv(a.d, kFinalCols) : 0))),
-                       dim3(kThreads), 0, s, (const float *)(ws + e.loss),
-                       (const float *)(ws + e.rel), (int)e.grid, a.d, loss, d_rel);
-    return hipGetLastError();
+    return final_sums(a, (const float *)(ws + e.loss), e.grid, (const float *)(ws + e.rel),
+                      (int)e.grid, loss, d_rel, s);
 }
 
 hipError_t gemm(const LpGemm &g, int64_t groups, hipStream_t s) {
@@ -1167,37 +1181,44 @@ hipError_t lp_loss(const LpArgs &a, const LpLayout &L, char *ws, float *loss, fl
         if (e.ok && a.batch * a.nn * a.d >= kEdgesMin && ((uintptr_t)d_emb & 15u) == 0)
             return lp_edges(a, e, ws, loss, pos, S, gpos, d_emb, d_rel, s);
     }
-    // (1) scores: u_i and the positives; per edge also the negatives
-    RGCN_HIP_TRY(bf ? dispatch_scores<true>(a, pos, S, U, dense ? 0 : 1, s)
-                    : dispatch_scores<false>(a, pos, S, U, dense ? 0 : 1, s));
+    // (1) scores: u_i, the positives' and the negatives' scores
     int64_t groups = 0, M = 0, N = 0;
     if (dense) {
         dense_shape(a, groups, M, N);
         const int64_t ncols = groups * N;
+        const dim3 grid((unsigned)grid_for(a.batch + (inbatch ? 0 : ncols), kThreads / 64));
         if (bf)
-            hipLaunchKernelGGL(k_lp_gather<true>, dim3((unsigned)grid_for(ncols * a.d, kThreads)),
-                               dim3(kThreads), 0, s, a, ncols, Hn);
+            hipLaunchKernelGGL(k_lp_shared_rows<true>, grid, dim3(kThreads), 0, s, a, ncols, pos, U, Hn);
         else
-            hipLaunchKernelGGL(k_lp_gather<false>, dim3((unsigned)grid_for(ncols * a.d, kThreads)),
-                               dim3(kThreads), 0, s, a, ncols, Hn);
+            hipLaunchKernelGGL(k_lp_shared_rows<false>, grid, dim3(kThreads), 0, s, a, ncols, pos, U, Hn);
         RGCN_HIP_TRY(hipGetLastError());
-        // S_g = U_g Hn_g^T  (rows: positives of the group; row stride N)
-        LpGemm g{};
-        g.A = U; g.B = Hn; g.C = S;
-        g.M = M; g.N = N; g.K = a.d;
-        g.sam = a.d; g.sak = 1; g.sbn = a.d; g.sbk = 1; g.scm = N; g.scn = 1;
-        g.bsa = M * a.d; g.bsb = N * a.d; g.bsc = M * N;
-        g.pos_total = a.batch; g.pos_per_group = M; g.pos_dim = 0;
-        RGCN_HIP_TRY(gemm(g, groups, s));
+        if (inbatch) {
+            RGCN_HIP_TRY(f32_scores(U, Hn, S, a.batch, a.batch, a.d, s));
+        } else {
+            // S_g = U_g Hn_g^T  (rows: positives of the group; row stride N)
+            LpGemm g{};
+            g.A = U; g.B = Hn; g.C = S;
+            g.M = M; g.N = N; g.K = a.d;
+            g.sam = a.d; g.sak = 1; g.sbn = a.d; g.sbk = 1; g.scm = N; g.scn = 1;
+            g.bsa = M * a.d; g.bsb = N * a.d; g.bsc = M * N;
+            g.pos_total = a.batch; g.pos_per_group = M; g.pos_dim = 0;
+            RGCN_HIP_TRY(gemm(g, groups, s));
+        }
+    } else {
+        RGCN_HIP_TRY(bf ? dispatch_scores<true>(a, pos, S, U, s)
+                        : dispatch_scores<false>(a, pos, S, U, s));
     }
-    // (2), (3) loss
+    // (2) loss per positive and the derivatives
     hipLaunchKernelGGL(k_lp_loss, dim3((unsigned)grid_for(a.batch, kThreads / 64)), dim3(kThreads),
-                       0, s, a, pos, S, gpos, Gm, lossp);
+                       0, s, a, pos, S, gpos, Gm, lossp, inbatch ? neg_score : nullptr);
     RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_lp_sum, dim3(1), dim3(kThreads), 0, s, lossp, a.batch, loss);
-    RGCN_HIP_TRY(hipGetLastError());
+    const int64_t parts = rel_parts(a.batch);
+    float *part = (float *)(ws + L.off_colsum);
     if (d_emb || d_rel) {
-        if (dense) {
+        if (inbatch) {
+            RGCN_HIP_TRY(f32_score_grads(Gm, Hn, U, dU, d_emb ? dHn : nullptr, a.batch, a.d, a.batch,
+                                         s));
+        } else if (dense) {
             // dU_g = G_g Hn_g: C[m][e] = sum_n G[m][n] Hn[n][e]
             LpGemm g{};
             g.A = Gm; g.B = Hn; g.C = dU;
@@ -1221,26 +1242,16 @@ hipError_t lp_loss(const LpArgs &a, const LpLayout &L, char *ws, float *loss, fl
                 RGCN_HIP_TRY(hipGetLastError());
             }
         }
-        RGCN_HIP_TRY(bf ? dispatch_finish<true>(a, gpos, Gm, U, dU, d_emb, P, s)
-                        : dispatch_finish<false>(a, gpos, Gm, U, dU, d_emb, P, s));
+        const float *cols = inbatch ? dHn : nullptr;
+        RGCN_HIP_TRY(bf ? dispatch_finish<true>(a, gpos, Gm, U, dU, cols, d_emb, P, s)
+                        : dispatch_finish<false>(a, gpos, Gm, U, dU, cols, d_emb, P, s));
         if (d_rel) {
-            const int64_t parts = rel_parts(a.batch);
-            const int64_t per = cdiv(a.batch, parts);
-            float *part = (float *)(ws + L.off_colsum);
             hipLaunchKernelGGL(k_lp_rel_partial, dim3((unsigned)cdiv(a.d, kRelCols), (unsigned)parts),
-                               dim3(kThreads), 0, s, P, a.batch, a.d, per, part);
-            RGCN_HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(k_lp_rel_final, dim3((unsigned)cdiv(a.d, kThreads)), dim3(kThreads), 0,
-                               s, part, parts, a.d, d_rel);
+                               dim3(kThreads), 0, s, P, a.batch, a.d, cdiv(a.batch, parts), part);
             RGCN_HIP_TRY(hipGetLastError());
         }
     }
-    if (neg_score && inbatch) {
-        hipLaunchKernelGGL(k_lp_offdiag, dim3((unsigned)grid_for(a.batch * a.nn, kThreads)),
-                           dim3(kThreads), 0, s, S, a.batch, neg_score);
-        RGCN_HIP_TRY(hipGetLastError());
-    }
-    return hipSuccess;
+    return final_sums(a, lossp, a.batch, part, (int)parts, loss, d_rel, s);
 }
 
 hipError_t lp_validate(const LpArgs &a, uint32_t *err, hipStream_t s) {

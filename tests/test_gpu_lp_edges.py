@@ -66,3 +66,14 @@ def test_forms_around_the_sorted_path():
     neg_s = torch.full((B, k), float("nan"), device="cuda")
     assert torch.equal(_call(emb, rel, src, dst, neg, k, neg_score=neg_s), want)
     assert bool(torch.isfinite(neg_s).all())
+
+
+@pytest.mark.parametrize("kind", [0, 2])
+@pytest.mark.parametrize("dtype,d,B", [("f32", 4, 2), ("f32", 260, 63), ("bf16", 8, 64),
+                                       ("bf16", 72, 65), ("f32", 36, 129), ("bf16", 520, 190)])
+def test_in_batch_tile_edges(dtype, d, B, kind):
+    """B x B score products at the edges of the 64 x 64 tiles and of 16-byte row pieces."""
+    emb, rel, src, dst, _, w = _case(d + B, dtype, 3 * B, d, B, 0, rgcn.RGCN_LP_NEG_IN_BATCH)
+    print(f"case lp in-batch loss={kind} {dtype} d={d} B={B}", flush=True)
+    got = _run(emb, rel, 2, kind, src, dst, 0, None, w)
+    _check(got, emb, rel, 2, kind, src, dst, 0, None, w)
