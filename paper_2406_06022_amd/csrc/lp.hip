@@ -519,6 +519,190 @@ __global__ __launch_bounds__(kThreads) void k_lp_negatives(int32_t mode, int64_t
     }
 }
 
+// ------------------------------------------------------------------ joint negatives, fused
+// Groups of at most 32 positives with their shared negatives, a workgroup per group and
+// everything in one pass: u_i and the negatives' rows in LDS as fp32 (row pitch DM + 1, so a
+// column over 32 rows touches distinct banks), the 32 x 32 scores on fp32 MFMA with K split
+// over the four waves, the loss and the derivatives, then per 32 columns dU_g = G_g H_g
+// and dH_g = G_g^T U_g straight into the gradient rows.  As passes over memory this took
+// ten launches for a few microseconds of work each.
+// Latency-bound (256 workgroups of one group each at B 8,192, K 32, d 256): 47 us with 16
+// waves per group and the rows' loads in flight together, 60 us with four waves.
+constexpr int kJointRows = 32;
+constexpr int kJointThreads = 1024;
+template <bool BF16, int DM>
+__global__ __launch_bounds__(kJointThreads) void k_lp_joint(LpArgs a, int64_t groups, float *pos,
+                                                       float *neg_score, float *part_loss,
+                                                       float *part_rel, float *d_emb, int grad) {
+    constexpr int P = DM + 1, R = kJointRows, GP = R + 1;
+    __shared__ float sU[R * P], sH[R * P], sP[4][R * GP], sG[R * GP], sRel[DM];
+    __shared__ float s_pos[R], s_gp[R], s_loss[kJointThreads / 64];
+    __shared__ int32_t s_src[R], s_dst[R], s_neg[R];
+    constexpr int NWV = kJointThreads / 64, E = DM / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int l32 = lane & 31, kh = lane >> 5;
+    const int d = a.d, K = (int)a.k;
+    const bool contrastive = a.loss == RGCN_LP_CONTRASTIVE;
+    const float inv_ce = (float)(1.0 / ((double)a.batch * (double)(1 + a.nn)));
+    for (int e = threadIdx.x; e < DM; e += kJointThreads) sRel[e] = 0.f;
+    float loss = 0.f;
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int64_t i0 = g * K;
+        const int m = a.batch - i0 < K ? (int)(a.batch - i0) : K;
+        if (threadIdx.x < R) {
+            const int t = threadIdx.x;
+            s_src[t] = t < m ? a.src[i0 + t] : 0;
+            s_dst[t] = t < m ? a.dst[i0 + t] : 0;
+            s_neg[t] = t < K ? a.neg[i0 + t] : 0;
+        }
+        __syncthreads();
+        // u_i and the positives' scores, and the negatives' rows: two rows of each per wave,
+        // all of their loads in flight together
+        {
+            float hs[2][E], hd[2][E], hn[2][E];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int row = wave + q * NWV;
+                const int64_t sr = s_src[row], dr = s_dst[row], nr = s_neg[row];
+#pragma unroll
+                for (int x = 0; x < E; ++x) {
+                    const int e = lane + 64 * x;
+                    hs[q][x] = e < d && row < m ? elem<BF16>(a, sr, e) : 0.f;
+                    hd[q][x] = e < d && row < m ? elem<BF16>(a, dr, e) : 0.f;
+                    hn[q][x] = e < d && row < K ? elem<BF16>(a, nr, e) : 0.f;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int row = wave + q * NWV;
+                float acc = 0.f;
+#pragma unroll
+                for (int x = 0; x < E; ++x) {
+                    const int e = lane + 64 * x;
+                    if (e >= d) continue;
+                    const float u = row < m ? hs[q][x] * rel_elem<BF16>(a, e) : 0.f;
+                    if (row < m) acc += u * hd[q][x];
+                    sU[row * P + e] = u;
+                    sH[row * P + e] = hn[q][x];
+                }
+                acc = group_sum(acc, 64);
+                if (lane == 0) {
+                    s_pos[row] = acc;
+                    if (row < m) pos[i0 + row] = acc;
+                }
+            }
+        }
+        __syncthreads();
+        // scores: lane l supplies row l % 32 of both operands at k = 2 s + l / 32 and holds
+        // column l % 32, rows 8 (e / 4) + 4 (l / 32) + e % 4
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        if (wave < 4) {
+#pragma unroll 4
+            for (int s = wave; s < d / 2; s += 4)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sU[l32 * P + 2 * s + kh], sH[l32 * P + 2 * s + kh],
+                                                       acc, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sP[wave][(8 * (e / 4) + 4 * kh + e % 4) * GP + l32] = acc[e];
+        }
+        __syncthreads();
+        // loss and derivatives: a wave per positive, lane k < K negative k
+        for (int row = wave; row < R; row += NWV) {
+            const bool okk = lane < K;
+            const int at = row * GP + l32;
+            const float s = sP[0][at] + sP[1][at] + sP[2][at] + sP[3][at];
+            float gk = 0.f, gp = 0.f;
+            if (row < m) {
+                const float sp = s_pos[row];
+                if (neg_score != nullptr && okk) neg_score[(i0 + row) * K + lane] = s;
+                if (contrastive) {
+                    float mx = okk ? fmaxf(sp, s) : sp;
+                    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                    const float x = okk ? expf(s - mx) : 0.f;
+                    float z = x;
+                    for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
+                    z += expf(sp - mx);
+                    const float inv = 1.f / (z * (float)a.batch);
+                    gk = x * inv;
+                    gp = expf(sp - mx) * inv - 1.f / (float)a.batch;
+                    if (lane == 0) loss += (mx + logf(z) - sp) / (float)a.batch;
+                } else {
+                    const float w = (a.loss == RGCN_LP_WEIGHTED_CE && a.pos_weight)
+                                        ? a.pos_weight[i0 + row] : 1.f;
+                    float l = okk ? softplus_f(s) : 0.f;
+                    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+                    gk = okk ? sigmoid_f(s) * inv_ce : 0.f;
+                    gp = w * (sigmoid_f(sp) - 1.f) * inv_ce;
+                    if (lane == 0) loss += (l + w * softplus_f(-sp)) * inv_ce;
+                }
+            }
+            if (lane < R) sG[at] = okk ? gk : 0.f;
+            if (lane == 0) s_gp[row] = gp;
+        }
+        __syncthreads();
+        if (grad) {
+            // a wave per 32 columns of dU (even tasks) or dH (odd)
+            for (int task = wave; task < 2 * ((d + 31) / 32); task += NWV) {
+                const int col = task / 2 * 32 + l32;
+                const bool okc = col < d, neg = task & 1;
+                const float *A = sG, *B = neg ? sU : sH;
+                f32x16 x;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) x[e] = 0.f;
+#pragma unroll
+                for (int s = 0; s < R / 2; ++s) {
+                    const int k = 2 * s + kh;
+                    x = __builtin_amdgcn_mfma_f32_32x32x2f32(A[neg ? k * GP + l32 : l32 * GP + k],
+                                                             okc ? B[k * P + col] : 0.f, x, 0, 0, 0);
+                }
+                if (neg) {
+                    if (okc && d_emb != nullptr)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int i = 8 * (e / 4) + 4 * kh + e % 4;
+                            if (i < K) unsafeAtomicAdd(d_emb + (int64_t)s_neg[i] * d + col, x[e]);
+                        }
+                    continue;
+                }
+                float drel = 0.f;
+                const float r = okc ? rel_elem<BF16>(a, col) : 0.f;
+                float hd[16], hs[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int i = 8 * (e / 4) + 4 * kh + e % 4;
+                    const bool ok = okc && i < m;
+                    hd[e] = ok ? elem<BF16>(a, s_dst[i], col) : 0.f;
+                    hs[e] = ok ? elem<BF16>(a, s_src[i], col) : 0.f;
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int i = 8 * (e / 4) + 4 * kh + e % 4;
+                    if (!okc || i >= m) continue;
+                    const float t = x[e] + s_gp[i] * hd[e];
+                    drel += t * hs[e];
+                    if (d_emb != nullptr) {
+                        unsafeAtomicAdd(d_emb + (int64_t)s_src[i] * d + col, t * r);
+                        unsafeAtomicAdd(d_emb + (int64_t)s_dst[i] * d + col, s_gp[i] * sU[i * P + col]);
+                    }
+                }
+                drel += __shfl_xor(drel, 32, 64);
+                if (okc && kh == 0) sRel[col] += drel;   // a column belongs to one wave
+            }
+        }
+        __syncthreads();   // the next group's rows take this one's space
+    }
+    if (lane == 0) s_loss[wave] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.f;
+        for (int w = 0; w < NWV; ++w) t += s_loss[w];
+        part_loss[blockIdx.x] = t;
+    }
+    if (grad && part_rel != nullptr)
+        for (int e = threadIdx.x; e < d; e += kJointThreads) part_rel[(int64_t)blockIdx.x * d + e] = sRel[e];
+}
+
 // ------------------------------------------------------------------ per-edge negatives
 // The path of large per-edge batches: scores, loss and every gradient with each negative's
 // row read once, and the embedding gradient summed row by row instead of by atomics.
@@ -1099,6 +1283,20 @@ hipError_t lp_edges(const LpArgs &a, const EdgePlan &e, char *ws, float *loss, f
                       (int)e.grid, loss, d_rel, s);
 }
 
+template <bool BF16, int DM>
+hipError_t run_joint(const LpArgs &a, char *ws, const LpLayout &L, int per_cu, float *loss, float *pos,
+                     float *neg_score, float *d_emb, float *d_rel, hipStream_t s) {
+    const int64_t groups = cdiv(a.batch, a.k);
+    const int64_t grid = groups < 256 * per_cu ? groups : 256 * per_cu;
+    // one partial row of d sums per workgroup, at most one per positive: the space of u
+    float *part_loss = (float *)(ws + L.off_lossp), *part_rel = (float *)(ws + L.off_U);
+    hipLaunchKernelGGL((k_lp_joint<BF16, DM>), dim3((unsigned)grid), dim3(kJointThreads), 0, s, a, groups,
+                       pos, neg_score, part_loss, d_rel ? part_rel : nullptr, d_emb,
+                       d_emb || d_rel ? 1 : 0);
+    RGCN_HIP_TRY(hipGetLastError());
+    return final_sums(a, part_loss, grid, part_rel, (int)grid, loss, d_rel, s);
+}
+
 hipError_t gemm(const LpGemm &g, int64_t groups, hipStream_t s) {
     if (groups == 0 || g.M == 0 || g.N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_lp_gemm, dim3((unsigned)cdiv(g.N, kLpTile), (unsigned)cdiv(g.M, kLpTile),
@@ -1180,6 +1378,20 @@ hipError_t lp_loss(const LpArgs &a, const LpLayout &L, char *ws, float *loss, fl
         const EdgePlan e = edge_plan(a, L);
         if (e.ok && a.batch * a.nn * a.d >= kEdgesMin && ((uintptr_t)d_emb & 15u) == 0)
             return lp_edges(a, e, ws, loss, pos, S, gpos, d_emb, d_rel, s);
+    }
+    // Joint groups of up to 32 positives whose rows fit LDS: one pass, where the groups fill
+    // at least half of its 32 rows or are few (measured, us, passes / fused: 8,192 x 32 x 256
+    // 88 / 55, 8,000 x 16 x 512 160 / 122, 1,024 x 32 x 512 74 / 57, 2,000 x 5 x 512 88 / 65;
+    // 16,384 x 10 x 256 160 / 174, 16,384 x 5 x 128 115 / 182, 1,000 x 1 x 64 38 / 46).
+    if (a.neg_mode == RGCN_LP_NEG_JOINT && a.k <= kJointRows && a.d <= 512 &&
+        (a.k >= 16 || cdiv(a.batch, a.k) <= 512)) {
+#define RGCN_JOINT(D_, W_)                                                                        \
+    return bf ? run_joint<true, D_>(a, ws, L, W_, loss, pos, neg_score, d_emb, d_rel, s)         \
+              : run_joint<false, D_>(a, ws, L, W_, loss, pos, neg_score, d_emb, d_rel, s)
+        if (a.d <= 128) RGCN_JOINT(128, 2);
+        if (a.d <= 256) RGCN_JOINT(256, 1);
+        RGCN_JOINT(512, 1);
+#undef RGCN_JOINT
     }
     // (1) scores: u_i, the positives' and the negatives' scores
     int64_t groups = 0, M = 0, N = 0;

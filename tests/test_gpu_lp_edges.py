@@ -77,3 +77,18 @@ def test_in_batch_tile_edges(dtype, d, B, kind):
     print(f"case lp in-batch loss={kind} {dtype} d={d} B={B}", flush=True)
     got = _run(emb, rel, 2, kind, src, dst, 0, None, w)
     _check(got, emb, rel, 2, kind, src, dst, 0, None, w)
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+@pytest.mark.parametrize("dtype,d,B,k", [
+    ("f32", 4, 40, 32), ("bf16", 128, 65, 32), ("f32", 132, 100, 31), ("bf16", 264, 33, 16),
+    ("f32", 512, 97, 17), ("bf16", 512, 1, 32), ("f32", 60, 700, 3), ("bf16", 520, 70, 32),
+    ("f32", 64, 70, 33), ("bf16", 64, 20_000, 16),
+])
+def test_joint_groups(dtype, d, B, k, kind):
+    """Joint groups around what one pass takes: 32 positives, width 512, ragged last groups,
+    and more groups than workgroups."""
+    emb, rel, src, dst, neg, w = _case(d + B + k, dtype, 500, d, B, k, rgcn.RGCN_LP_NEG_JOINT)
+    print(f"case lp joint loss={kind} {dtype} d={d} B={B} k={k}", flush=True)
+    got = _run(emb, rel, 1, kind, src, dst, k, neg, w)
+    _check(got, emb, rel, 1, kind, src, dst, k, neg, w)
