@@ -245,17 +245,20 @@ struct SampleTab {
     int32_t ntypes, nrel, fanout, layer;
     uint64_t seed;
     int64_t n_seg, cap_total;
-    int64_t num_nodes[kMaxTypes], n_dst[kMaxTypes], type_base[kMaxTypes], type_cap[kMaxTypes];
+    int64_t num_nodes[kMaxTypes], n_dst[kMaxTypes], type_cap[kMaxTypes];
     int64_t node_base[kMaxTypes];   // prefix of num_nodes (the per-node first-position words)
     const int64_t *dst_ids[kMaxTypes];
     int64_t *out_src_ids[kMaxTypes];
     int32_t src_type[kMaxRels], dst_type[kMaxRels];
-    int64_t seg_base[kMaxRels], cand_base[kMaxRels];
+    int64_t seg_base[kMaxRels];
     const int64_t *g_indptr[kMaxRels];
     const int64_t *g_indices[kMaxRels];
     int32_t *out_indptr[kMaxRels];
     int32_t *out_indices[kMaxRels];
     int64_t *out_src_rows[kMaxRels];   // global source id per sampled edge, or NULL
+    // candidate runs in order: per type its destination rows (relation -1), then its relations
+    int32_t nrun;
+    int16_t run_type[kMaxRels + kMaxTypes], run_rel[kMaxRels + kMaxTypes];
 };
 struct SampleLayout {
     size_t off_err, off_tab, off_seg, off_scan, off_cand, off_flag, off_first, total;

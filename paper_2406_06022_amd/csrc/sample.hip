@@ -10,14 +10,23 @@
 // edges are relabelled to those block-local rows.
 //
 // Layout of the work: every (relation, destination row) is a segment; a count pass and
-// an exclusive scan give each segment's edge offset; the draw pass writes the sampled
-// global ids into a candidate array laid out per source type by capacity (destination
-// ids first, then each relation leaving the type, fanout slots per destination row), so
-// candidate positions follow first-appearance order with gaps.  One word per graph node
+// an exclusive scan give each segment's edge offset; the draw passes write the sampled
+// global ids into a candidate array grouped by source type (destination ids first, then the
+// edges of each relation leaving the type), so candidate positions follow first-appearance
+// order.  Its runs start where the counts say (known on the device only), with no gaps: at
+// in-degrees well below the fanout most of an array laid out by capacity is empty slots,
+// and every later pass walked them.  One word per graph node
 // keeps the smallest position holding that node (atomicMin: one atomic per candidate, no
 // probing, where a hash table keyed by id needs a compare-and-swap and a min per
 // candidate); a flag per position that holds its
 // node's first occurrence, scanned, numbers the source rows.
+//
+// Bound by random 4- and 8-byte accesses and atomics and by their latency, far from the
+// bandwidth of the 12 bytes per sampled edge.  16,384 seeds, fanouts 25 and 15, a graph of
+// 13M nodes (5M sampled edges in the second layer): 1,040 us of kernels by capacity with a
+// thread per segment, 680 us so, 400 of them the draws and their atomics.
+#include <string.h>
+
 #include "common.h"
 
 namespace rgcn {
@@ -70,12 +79,15 @@ __device__ __forceinline__ bool seg_of(const SampleTab &T, int64_t s, Seg &g, ui
     return true;
 }
 
+// Edges per segment, and beside it first[node] = INT32_MAX for every graph node.
 __global__ __launch_bounds__(kThreads) void k_sample_count(const SampleTab *tab, int32_t *cnt,
-                                                           uint32_t *err) {
+                                                           uint32_t *err, int32_t *first,
+                                                           int64_t nodes) {
     __shared__ SampleTab T;
     load_tab(&T, tab);
-    for (int64_t s = (int64_t)blockIdx.x * kThreads + threadIdx.x; s <= T.n_seg;
-         s += (int64_t)gridDim.x * kThreads) {
+    const int64_t i0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kThreads;
+    for (int64_t s = i0; s <= T.n_seg; s += stride) {
         if (s == T.n_seg) {
             cnt[s] = 0;
             continue;
@@ -84,56 +96,167 @@ __global__ __launch_bounds__(kThreads) void k_sample_count(const SampleTab *tab,
         seg_of(T, s, g, err);
         cnt[s] = (int32_t)(g.deg < T.fanout ? g.deg : T.fanout);
     }
+    const int big = 0x7FFFFFFF;
+    int4 *f4 = (int4 *)first;
+    for (int64_t i = i0; i < nodes / 4; i += stride) f4[i] = make_int4(big, big, big, big);
+    for (int64_t i = nodes / 4 * 4 + i0; i < nodes; i += stride) first[i] = big;
 }
 
-// Destination ids of each type at the head of its candidate region.
-__global__ __launch_bounds__(kThreads) void k_sample_prefix(const SampleTab *tab, int64_t *cand) {
-    __shared__ SampleTab T;
-    load_tab(&T, tab);
-    for (int t = 0; t < T.ntypes; ++t)
-        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < T.n_dst[t];
-             i += (int64_t)gridDim.x * kThreads)
-        {
-            const int64_t v = T.dst_ids[t][i];   // out of range: reported by the count pass
-            cand[T.type_base[t] + i] = (v >= 0 && v < T.num_nodes[t]) ? v : 0;
+// The candidate array's runs in order (per type its destination rows, then the edges of each
+// relation leaving it), their first positions from the segments' offsets; start[nrun] = the
+// end.  Every thread of the workgroup calls it.
+struct Runs {
+    int32_t start[kMaxRels + kMaxTypes + 1];
+    int32_t rel_start[kMaxRels];
+};
+__device__ __forceinline__ void load_runs(const SampleTab &T, const int32_t *off, Runs &R) {
+    for (int k = threadIdx.x; k < T.nrun; k += blockDim.x) {
+        const int r = T.run_rel[k];
+        R.start[k + 1] = r < 0 ? (int32_t)T.n_dst[T.run_type[k]]
+                               : off[T.seg_base[r] + T.n_dst[T.dst_type[r]]] - off[T.seg_base[r]];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        R.start[0] = 0;
+        for (int k = 0; k < T.nrun; ++k) {
+            if (T.run_rel[k] >= 0) R.rel_start[T.run_rel[k]] = R.start[k];
+            R.start[k + 1] += R.start[k];
         }
+    }
+    __syncthreads();
+}
+// Run of candidate position p (the last that starts at or before it; empty runs end there).
+__device__ __forceinline__ int run_of(const SampleTab &T, const Runs &R, int32_t p) {
+    int lo = 0, hi = T.nrun - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (R.start[mid] <= p) lo = mid; else hi = mid - 1;
+    }
+    return lo;
 }
 
-// One thread per segment: the positions taken (sorted, in LDS, one column per thread),
-// then the global ids of those in-edges into the candidate array, and the block indptr.
-__global__ __launch_bounds__(kDrawThreads) void k_sample_draw(const SampleTab *tab,
-                                                              const int32_t *off, int64_t *cand,
-                                                              uint32_t *err) {
+// A candidate: its id, and first[node_base[t] + id], the smallest candidate position holding
+// node id of type t (INT32_MAX: none; cleared by the count pass).  Taken where the id is
+// drawn: in a pass of its own the atomics waited on nothing else (draw, floyd and that pass
+// 454 us, 401 so).
+__device__ __forceinline__ void put(int64_t *cand, int32_t *first, int64_t node_base, int64_t p,
+                                    int64_t id) {
+    cand[p] = id;
+    atomicMin(&first[node_base + id], (int32_t)p);
+}
+
+// Segments of at most fanout in-edges, edge by edge: a wave takes 64 consecutive segments,
+// whose sampled edges are one contiguous range, and walks it 64 edges at a time, each lane
+// finding its edge's segment by a binary search over the lanes' offsets.  Segments that are
+// sampled are listed for k_sample_floyd (a few per wave: drawn here, their lanes held
+// up the whole wave).  Also the block indptr, the relations' edge counts and the
+// destination ids at the head of each type's candidates.
+__global__ __launch_bounds__(kThreads) void k_sample_draw(const SampleTab *tab, const int32_t *off,
+                                                          int64_t *cand, int32_t *first,
+                                                          int64_t *counts, int32_t *heavy, uint32_t *nheavy,
+                                                          uint32_t *err) {
     __shared__ SampleTab T;
+    __shared__ Runs R;
+    load_tab(&T, tab);
+    load_runs(T, off, R);
+    const int lane = threadIdx.x & 63;
+    if (blockIdx.x == 0)
+        for (int r = threadIdx.x; r < T.nrel; r += kThreads) {
+            const int64_t n = T.n_dst[T.dst_type[r]];
+            const int32_t tot = off[T.seg_base[r] + n] - off[T.seg_base[r]];
+            T.out_indptr[r][n] = tot;
+            counts[r] = tot;
+        }
+    for (int k = 0; k < T.nrun; ++k) {
+        if (T.run_rel[k] >= 0) continue;
+        const int t = T.run_type[k];
+        for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < T.n_dst[t];
+             i += (int64_t)gridDim.x * kThreads) {
+            const int64_t v = T.dst_ids[t][i];   // out of range: reported by the count pass
+            put(cand, first, T.node_base[t], R.start[k] + i,
+                (v >= 0 && v < T.num_nodes[t]) ? v : 0);
+        }
+    }
+    const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
+    for (int64_t s0 = (((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6) * 64; s0 < T.n_seg;
+         s0 += waves * 64) {
+        const int64_t s = s0 + lane;
+        const bool live = s < T.n_seg;
+        Seg g;
+        g.r = 0;
+        g.i = g.v = g.base = g.deg = 0;
+        int32_t eb = 0, ee = 0;
+        if (live) {
+            seg_of(T, s, g, err);
+            eb = off[s];
+            ee = off[s + 1];
+            T.out_indptr[g.r][g.i] = eb - off[T.seg_base[g.r]];
+        }
+        const bool drawn = live && g.deg > T.fanout && ee > eb;
+        const uint64_t dm = __ballot(drawn);
+        if (dm != 0) {
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(nheavy, (uint32_t)__popcll(dm));
+            at = __shfl(at, 0, 64);
+            if (drawn) heavy[at + lanes_below(dm)] = (int32_t)s;
+        }
+        // position of the segment's first candidate, less its first edge
+        const int64_t shift = live ? (int64_t)R.rel_start[g.r] - off[T.seg_base[g.r]] : 0;
+        const int last = (int)((T.n_seg - s0 < 64 ? T.n_seg - s0 : 64) - 1);
+        // unsigned: edges up to 2^31 - 2, the loop's last step goes past them
+        const uint32_t E0 = (uint32_t)__shfl(eb, 0, 64), E1 = (uint32_t)__shfl(ee, last, 64);
+        const uint32_t ebs = live ? (uint32_t)eb : 0xFFFFFFFFu;   // dead lanes never match
+        for (uint32_t e0 = E0; e0 < E1; e0 += 64) {
+            const uint32_t e = e0 + lane;
+            int lo = 0;
+#pragma unroll
+            for (int step = 32; step >= 1; step >>= 1) {
+                const int c = lo + step;
+                const uint32_t v = (uint32_t)__shfl((int)ebs, c, 64);
+                if (v <= e) lo = c;
+            }
+            const int rg = __shfl(g.r, lo, 64);
+            const int64_t base = shfl64(g.base, lo), sh = shfl64(shift, lo);
+            const uint32_t first_e = (uint32_t)__shfl(eb, lo, 64);
+            const bool skip = (dm >> lo) & 1u;
+            if (e < E1 && !skip) {
+                int64_t x = T.g_indices[rg][base + (e - first_e)];
+                const int t = T.src_type[rg];
+                if (x < 0 || x >= T.num_nodes[t]) {
+                    atomicOr(err, 8u);
+                    x = 0;
+                }
+                put(cand, first, T.node_base[t], (int64_t)e + sh, x);
+            }
+        }
+    }
+}
+
+// The listed segments, one thread each: the positions taken (sorted, in LDS, one column per
+// thread), then the global ids of those in-edges into the candidate array.
+__global__ __launch_bounds__(kDrawThreads) void k_sample_floyd(const SampleTab *tab,
+                                                               const int32_t *off, int64_t *cand,
+                                                               int32_t *first, const int32_t *heavy,
+                                                               const uint32_t *nheavy,
+                                                               uint32_t *err) {
+    const int64_t n = *nheavy;
+    if ((int64_t)blockIdx.x * kDrawThreads >= n) return;
+    __shared__ SampleTab T;
+    __shared__ Runs R;
     __shared__ uint32_t pos[kMaxFanout][kDrawThreads];
     load_tab(&T, tab);
+    load_runs(T, off, R);
     const int lane = threadIdx.x;
-    for (int64_t s = (int64_t)blockIdx.x * kDrawThreads + lane; s < T.n_seg;
-         s += (int64_t)gridDim.x * kDrawThreads) {
+    for (int64_t h = (int64_t)blockIdx.x * kDrawThreads + lane; h < n;
+         h += (int64_t)gridDim.x * kDrawThreads) {
+        const int64_t s = heavy[h];
         Seg g;
         seg_of(T, s, g, err);
         const int r = g.r;
-        const int64_t e = (int64_t)off[s] - off[T.seg_base[r]];
-        T.out_indptr[r][g.i] = (int32_t)e;
         const int f = T.fanout;
-        const int c = off[s + 1] - off[s];
-        if (c == 0) continue;
-        const int src = T.src_type[r];
+        const int64_t nsrc = T.num_nodes[T.src_type[r]];
         const int64_t *gx = T.g_indices[r];
-        int64_t *out = cand + T.cand_base[r] + e;
-        const int64_t nsrc = T.num_nodes[src];
-        auto put = [&](int q, int64_t p) {
-            int64_t x = gx[g.base + p];
-            if (x < 0 || x >= nsrc) {
-                atomicOr(err, 8u);
-                x = 0;
-            }
-            out[q] = x;
-        };
-        if (g.deg <= f) {
-            for (int q = 0; q < c; ++q) put(q, q);
-            continue;
-        }
+        const int64_t out = (int64_t)R.rel_start[r] + (off[s] - off[T.seg_base[r]]);
         // Floyd: for j = deg - f .. deg - 1, t uniform in [0, j]; take t, or j when t is
         // already taken (j exceeds every position taken so far, so it goes last).
         int taken = 0;
@@ -162,118 +285,89 @@ __global__ __launch_bounds__(kDrawThreads) void k_sample_draw(const SampleTab *t
             }
             ++taken;
         }
-        for (int q = 0; q < f; ++q) put(q, pos[q][lane]);
+#pragma unroll 4
+        for (int q = 0; q < f; ++q) {
+            int64_t x = gx[g.base + pos[q][lane]];
+            if (x < 0 || x >= nsrc) {
+                atomicOr(err, 8u);
+                x = 0;
+            }
+            put(cand, first, T.node_base[T.src_type[r]], out + q, x);
+        }
     }
 }
 
-// Per relation: the last indptr entry and the edge count; per type the source count is
-// written by k_dedup_counts.
-__global__ void k_sample_tails(const SampleTab *tab, const int32_t *off, int64_t *counts) {
-    __shared__ SampleTab T;
-    load_tab(&T, tab);
-    for (int r = threadIdx.x; r < T.nrel; r += blockDim.x) {
-        const int64_t n = T.n_dst[T.dst_type[r]];
-        const int32_t tot = off[T.seg_base[r] + n] - off[T.seg_base[r]];
-        T.out_indptr[r][n] = tot;
-        counts[r] = tot;
-    }
+// Whether a position is its node's first, as one bit a position with a count per word of 64:
+// the scan that follows runs over the counts alone, and the emit pass reads ranks from
+// 12 bytes per 64 positions, which its L2 holds (a 4-byte flag and rank per position:
+// flag and scan passes 167 us, emit 118; so 116 and 95, at the shape above).
+struct FirstBits {
+    uint64_t *bits;
+    int32_t *cnt;    // counts, then their exclusive scan; one more than the words
+    int64_t words;   // positions 0 .. cap_total
+};
+__device__ __forceinline__ int32_t rank_of(const FirstBits &F, int32_t p) {
+    return F.cnt[p >> 6] + __popcll(F.bits[p >> 6] & ((1ull << (p & 63)) - 1));
 }
-
-// Candidate position p -> type, relation (-1: destination prefix) and edge; false for
-// the unused capacity slots.
-__device__ __forceinline__ bool slot_info(const SampleTab &T, const int32_t *off, int64_t p,
-                                          int &t, int &r, int64_t &e) {
-    t = find_le(T.type_base, T.ntypes, p);
-    const int64_t q = p - T.type_base[t];
-    if (q < T.n_dst[t]) {
-        r = -1;
-        e = q;
-        return true;
-    }
-    r = -1;
-    for (int x = 0; x < T.nrel; ++x)
-        if (T.src_type[x] == t && p >= T.cand_base[x]) r = x;
-    if (r < 0) return false;
-    e = p - T.cand_base[r];
-    const int64_t tot = off[T.seg_base[r] + T.n_dst[T.dst_type[r]]] - off[T.seg_base[r]];
-    return e < tot;
-}
-
-// first[node_base[t] + id]: the smallest candidate position holding node id of type t
-// (INT32_MAX: none), one word per graph node, cleared every call.
-__global__ __launch_bounds__(kThreads) void k_fill_first(int32_t *first, int64_t n) {
-    const int64_t n4 = n / 4;
-    int4 *f4 = (int4 *)first;
-    const int big = 0x7FFFFFFF;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n4;
-         i += (int64_t)gridDim.x * kThreads)
-        f4[i] = make_int4(big, big, big, big);
-    for (int64_t i = n4 * 4 + (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * kThreads)
-        first[i] = big;
-}
-
-__global__ __launch_bounds__(kThreads) void k_dedup_insert(const SampleTab *tab, const int32_t *off,
-                                                           const int64_t *cand, int32_t *first) {
-    __shared__ SampleTab T;
-    load_tab(&T, tab);
-    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < T.cap_total;
-         p += (int64_t)gridDim.x * kThreads) {
-        int t, r;
-        int64_t e;
-        if (!slot_info(T, off, p, t, r, e)) continue;
-        atomicMin(&first[T.node_base[t] + cand[p]], (int32_t)p);
-    }
-}
-
 __global__ __launch_bounds__(kThreads) void k_dedup_flag(const SampleTab *tab, const int32_t *off,
                                                          const int64_t *cand, const int32_t *first,
-                                                         int32_t *flag, uint32_t *err) {
+                                                         FirstBits F, uint32_t *err) {
     __shared__ SampleTab T;
+    __shared__ Runs R;
     load_tab(&T, tab);
-    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p <= T.cap_total;
-         p += (int64_t)gridDim.x * kThreads) {
-        if (p == T.cap_total) {
-            flag[p] = 0;
-            continue;
+    load_runs(T, off, R);
+    const int64_t total = R.start[T.nrun];
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
+    for (int64_t w = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6; w <= F.words;
+         w += waves) {
+        const int64_t p = w * 64 + lane;
+        bool f = false;
+        if (p < total) {
+            const int k = run_of(T, R, (int32_t)p);
+            f = first[T.node_base[T.run_type[k]] + cand[p]] == (int32_t)p;
+            if (T.run_rel[k] < 0 && !f) atomicOr(err, 2u);   // a repeated destination id
         }
-        int t, r;
-        int64_t e;
-        if (!slot_info(T, off, p, t, r, e)) {
-            flag[p] = 0;
-            continue;
+        const uint64_t m = __ballot(f);
+        if (lane == 0) {
+            if (w < F.words) F.bits[w] = m;
+            F.cnt[w] = __popcll(m);
         }
-        const int32_t f = first[T.node_base[t] + cand[p]] == (int32_t)p ? 1 : 0;
-        flag[p] = f;
-        if (r < 0 && !f) atomicOr(err, 2u);   // a repeated destination id
     }
 }
 
+// Block-local rows of every edge, the source ids in order of first appearance, and the
+// number of source nodes per type.
 __global__ __launch_bounds__(kThreads) void k_dedup_emit(const SampleTab *tab, const int32_t *off,
                                                          const int64_t *cand,
-                                                         const int32_t *first,
-                                                         const int32_t *rank) {
+                                                         const int32_t *first, FirstBits F,
+                                                         int64_t *counts) {
     __shared__ SampleTab T;
+    __shared__ Runs R;
+    __shared__ int32_t s_base[kMaxTypes + 1];   // rank at each type's first position
     load_tab(&T, tab);
-    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < T.cap_total;
+    load_runs(T, off, R);
+    const int64_t total = R.start[T.nrun];
+    for (int k = threadIdx.x; k < T.nrun; k += kThreads)
+        if (T.run_rel[k] < 0) s_base[T.run_type[k]] = rank_of(F, R.start[k]);
+    if (threadIdx.x == 0) s_base[T.ntypes] = rank_of(F, (int32_t)total);
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < T.ntypes)
+        counts[T.nrel + threadIdx.x] = s_base[threadIdx.x + 1] - s_base[threadIdx.x];
+    for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < total;
          p += (int64_t)gridDim.x * kThreads) {
-        int t, r;
-        int64_t e;
-        if (!slot_info(T, off, p, t, r, e)) continue;
+        const int k = run_of(T, R, (int32_t)p);
+        const int t = T.run_type[k], r = T.run_rel[k];
         const int64_t id = cand[p];
         const int32_t f = first[T.node_base[t] + id];
-        const int32_t loc = rank[f] - rank[T.type_base[t]];
+        const int32_t loc = rank_of(F, f) - s_base[t];
         if (f == (int32_t)p) T.out_src_ids[t][loc] = id;
-        if (r >= 0) T.out_indices[r][e] = loc;
-        if (r >= 0 && T.out_src_rows[r]) T.out_src_rows[r][e] = id;
+        if (r >= 0) {
+            const int64_t e = p - R.start[k];
+            T.out_indices[r][e] = loc;
+            if (T.out_src_rows[r]) T.out_src_rows[r][e] = id;
+        }
     }
-}
-
-__global__ void k_dedup_counts(const SampleTab *tab, const int32_t *rank, int64_t *counts) {
-    __shared__ SampleTab T;
-    load_tab(&T, tab);
-    for (int t = threadIdx.x; t < T.ntypes; t += blockDim.x)
-        counts[T.nrel + t] = rank[T.type_base[t] + T.type_cap[t]] - rank[T.type_base[t]];
 }
 
 // Grid-stride launches: at most 8 workgroups per CU of 256 (each copies the tables).
@@ -295,18 +389,23 @@ bool sample_layout(SampleTab &T, SampleLayout &L) {
     T.n_seg = s;
     int64_t c = 0;
     for (int t = 0; t < T.ntypes; ++t) {
-        T.type_base[t] = c;
         int64_t cap = T.n_dst[t];
         for (int r = 0; r < T.nrel; ++r)
-            if (T.src_type[r] == t) {
-                T.cand_base[r] = c + cap;
-                cap += T.n_dst[T.dst_type[r]] * (int64_t)T.fanout;
-            }
+            if (T.src_type[r] == t) cap += T.n_dst[T.dst_type[r]] * (int64_t)T.fanout;
         T.type_cap[t] = cap;
         c += cap;
     }
-    for (int t = T.ntypes; t < kMaxTypes; ++t) T.type_base[t] = c, T.type_cap[t] = 0;
     T.cap_total = c;
+    T.nrun = 0;
+    for (int t = 0; t < T.ntypes; ++t) {
+        T.run_type[T.nrun] = (int16_t)t;
+        T.run_rel[T.nrun++] = -1;
+        for (int r = 0; r < T.nrel; ++r)
+            if (T.src_type[r] == t) {
+                T.run_type[T.nrun] = (int16_t)t;
+                T.run_rel[T.nrun++] = (int16_t)r;
+            }
+    }
     if (T.n_seg + 1 > 0x7FFFFFFFll || c + 1 > 0x7FFFFFFFll) return false;
     int64_t nodes = 0;
     for (int t = 0; t < T.ntypes; ++t) {
@@ -336,37 +435,44 @@ hipError_t sample_block(const SampleTab &T, const SampleLayout &L, char *ws, int
     int64_t *cand = (int64_t *)(ws + L.off_cand);
     int32_t *flag = (int32_t *)(ws + L.off_flag);
     int32_t *first = (int32_t *)(ws + L.off_first);
-    const uint32_t zero = 0;
-    RGCN_HIP_TRY(fill_words(err, &zero, 4, s));
-    RGCN_HIP_TRY(fill_words(tab, &T, sizeof(SampleTab), s));
-    hipLaunchKernelGGL(k_sample_count, dim3((unsigned)grid_for(T.n_seg + 1, kThreads)),
-                       dim3(kThreads), 0, s, tab, seg, err);
+    // the error word, the list's length behind it, and the tables: one region, one fill
+    struct {
+        uint32_t words[64];
+        SampleTab tab;
+    } head;
+    static_assert(sizeof(head.words) == 256, "off_tab follows off_err");
+    memset(head.words, 0, sizeof(head.words));
+    head.tab = T;
+    RGCN_HIP_TRY(fill_words(err, &head, sizeof(head.words) + sizeof(SampleTab), s));
+    uint32_t *nheavy = err + 1;
+    int32_t *heavy = flag;   // the flags are written after the list is read
+    int64_t count_items = L.nodes / 4 > T.n_seg + 1 ? L.nodes / 4 : T.n_seg + 1;
+    hipLaunchKernelGGL(k_sample_count, dim3((unsigned)grid_for(count_items, kThreads)),
+                       dim3(kThreads), 0, s, tab, seg, err, first, L.nodes);
     RGCN_HIP_TRY(hipGetLastError());
     RGCN_HIP_TRY(exclusive_scan_i32(seg, seg, T.n_seg + 1, ws + L.off_scan, s));
-    int64_t maxdst = 0;
+    int64_t maxdst = T.n_seg;
     for (int t = 0; t < T.ntypes; ++t) maxdst = T.n_dst[t] > maxdst ? T.n_dst[t] : maxdst;
-    hipLaunchKernelGGL(k_sample_prefix, dim3((unsigned)grid_for(maxdst, kThreads)),
-                       dim3(kThreads), 0, s, tab, cand);
+    hipLaunchKernelGGL(k_sample_draw, dim3((unsigned)grid_for(maxdst, kThreads)), dim3(kThreads), 0,
+                       s, tab, seg, cand, first, counts, heavy, nheavy, err);
     RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_sample_draw, dim3((unsigned)grid_for(T.n_seg, kDrawThreads)),
-                       dim3(kDrawThreads), 0, s, tab, seg, cand, err);
+    if (T.n_seg > 0) {
+        hipLaunchKernelGGL(k_sample_floyd, dim3((unsigned)grid_for(T.n_seg, kDrawThreads)),
+                           dim3(kDrawThreads), 0, s, tab, seg, cand, first, heavy, nheavy,
+                           err);
+        RGCN_HIP_TRY(hipGetLastError());
+    }
+    // 12 bytes a word within the 4 a position of the flags' region (256 bytes at least)
+    FirstBits F;
+    F.words = T.cap_total / 64 + 1;
+    F.bits = (uint64_t *)flag;
+    F.cnt = (int32_t *)(F.bits + F.words);
+    hipLaunchKernelGGL(k_dedup_flag, dim3((unsigned)grid_for((F.words + 1) * 64, kThreads)),
+                       dim3(kThreads), 0, s, tab, seg, cand, first, F, err);
     RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_sample_tails, dim3(1), dim3(64), 0, s, tab, seg, counts);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_fill_first, dim3((unsigned)grid_for(L.nodes / 4 + 1, kThreads)),
-                       dim3(kThreads), 0, s, first, L.nodes);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_dedup_insert, dim3((unsigned)grid_for(T.cap_total, kThreads)),
-                       dim3(kThreads), 0, s, tab, seg, cand, first);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_dedup_flag, dim3((unsigned)grid_for(T.cap_total + 1, kThreads)),
-                       dim3(kThreads), 0, s, tab, seg, cand, first, flag, err);
-    RGCN_HIP_TRY(hipGetLastError());
-    RGCN_HIP_TRY(exclusive_scan_i32(flag, flag, T.cap_total + 1, ws + L.off_scan, s));
+    RGCN_HIP_TRY(exclusive_scan_i32(F.cnt, F.cnt, F.words + 1, ws + L.off_scan, s));
     hipLaunchKernelGGL(k_dedup_emit, dim3((unsigned)grid_for(T.cap_total, kThreads)),
-                       dim3(kThreads), 0, s, tab, seg, cand, first, flag);
-    RGCN_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_dedup_counts, dim3(1), dim3(64), 0, s, tab, flag, counts);
+                       dim3(kThreads), 0, s, tab, seg, cand, first, F, counts);
     return hipGetLastError();
 }
 

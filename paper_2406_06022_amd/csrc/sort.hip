@@ -819,9 +819,10 @@ __global__ __launch_bounds__(kThreads) void k_bwd_init(int32_t *p, int64_t n, ui
     if (t < n) p[t] = 0;
 }
 
+constexpr int kFillWords = 992;   // within the 4 KB of kernel arguments
 struct Words {
     uint32_t n;
-    uint32_t w[512];
+    uint32_t w[kFillWords];
 };
 __global__ void k_fill_words(uint32_t *dst, Words a) {
     for (uint32_t i = threadIdx.x; i < a.n; i += blockDim.x) dst[i] = a.w[i];
@@ -1042,9 +1043,9 @@ hipError_t bwd_plan(const CscRels &rels, int64_t total_rows, int64_t nnz, int64_
 hipError_t fill_words(void *dst, const void *src_host, size_t bytes, hipStream_t s) {
     const uint32_t *src = (const uint32_t *)src_host;
     size_t nw = bytes / 4;
-    for (size_t off = 0; off < nw; off += 512) {
+    for (size_t off = 0; off < nw; off += kFillWords) {
         Words a;
-        a.n = (uint32_t)((nw - off) < 512 ? (nw - off) : 512);
+        a.n = (uint32_t)((nw - off) < kFillWords ? (nw - off) : kFillWords);
         for (uint32_t i = 0; i < a.n; ++i) a.w[i] = src[off + i];
         hipLaunchKernelGGL(k_fill_words, dim3(1), dim3(256), 0, s, (uint32_t *)dst + off, a);
         RGCN_HIP_TRY(hipGetLastError());

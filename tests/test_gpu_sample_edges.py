@@ -1,0 +1,43 @@
+"""Block sampling at the edges of its walks, against the sampling oracle, bit for bit.
+
+Copied segments are walked 64 edges at a time by waves of 64 segments, sampled ones are
+listed and drawn apart, and first appearances are one bit a position in words of 64: one
+destination, counts around 64, no edges at all, every segment sampled, and none.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2406_06022_amd import rgcn, synth
+
+pytestmark = pytest.mark.gpu
+
+RELS = [(0, 1), (1, 0), (0, 0), (2, 1)]
+
+
+@pytest.mark.parametrize("n_dst,fanout,mean", [
+    (1, 4, 4.0), (63, 3, 3.0), (64, 3, 3.0), (65, 3, 3.0), (64, 1, 1.0), (64, 5, 0.0),
+    (127, 64, 8.0), (128, 1, 90.0), (257, 7, 7.0), (2049, 2, 2.0)])
+def test_edges_bit_exact(n_dst, fanout, mean):
+    rng = np.random.default_rng(n_dst * 100 + fanout)
+    g = synth.random_graph(rng, [2500, 2100, 300], RELS, mean, heavy=0, heavy_deg=0)
+    dg = rgcn.DeviceGraph(g)
+    dst = [rng.choice(2500, n_dst, replace=False).astype(np.int64),
+           rng.choice(2100, max(n_dst // 2, 1), replace=False).astype(np.int64),
+           np.zeros(0, np.int64)]
+    print(f"case sample edges n_dst={n_dst} fanout={fanout} mean={mean}", flush=True)
+    ip, ix, src, counts, rows = rgcn.rgcn_sample_block(
+        dg, [torch.as_tensor(x).cuda() for x in dst], fanout, 5, 2,
+        flags=rgcn.RGCN_VALIDATE_DEVICE, src_rows=True)
+    torch.cuda.synchronize()
+    c = counts.cpu().numpy()
+    ref = oracle.sample_block(g, dst, fanout, 5, 2)
+    for r, (s, _) in enumerate(RELS):
+        assert c[r] == ref.rels[r].indices.shape[0]
+        assert np.array_equal(ip[r].cpu().numpy(), ref.rels[r].indptr)
+        assert np.array_equal(ix[r][: c[r]].cpu().numpy(), ref.rels[r].indices)
+        assert np.array_equal(rows[r][: c[r]].cpu().numpy(), ref.src_ids[s][ref.rels[r].indices])
+    for t in range(3):
+        assert c[len(RELS) + t] == ref.n_src[t]
+        assert np.array_equal(src[t][: c[len(RELS) + t]].cpu().numpy(), ref.src_ids[t])
