@@ -422,34 +422,29 @@ LP_SETTINGS = ["contrastive / in-batch, B 1024", "cross entropy / in-batch, B 10
 def summarize_lp(args) -> str:
     """Kernel time per decoder call for each setting measure_lp runs (3 untimed and 50
     timed calls per B 1024 setting, 3 and 10 for the large batch, in that order; a call
-    starts with its k_lp_scores launch)."""
+    ends with its k_lp_final launch)."""
     calls, cur = [], []
-    for _, name, v in _dispatches(args.summarize_lp, r"rgcn::.*k_lp_"):
-        base = re.sub(r"<.*$", "", name)
-        if base == "k_lp_scores" and cur:
+    for _, name, v in _dispatches(args.summarize_lp, r"rgcn::"):
+        base = re.sub(r"[<(].*$", "", name)
+        if base == "k_lp_negatives":
+            continue
+        cur.append((base, v / 1e3))
+        if base == "k_lp_final":
             calls.append(cur)
             cur = []
-        cur.append((base, v / 1e3))
-    calls.append(cur)
-    keys = [("scores", ["k_lp_scores"]), ("gather", ["k_lp_gather"]), ("gemm (3)", ["k_lp_gemm"]),
-            ("loss", ["k_lp_loss"]), ("sum", ["k_lp_sum"]), ("scatter", ["k_lp_scatter_cols"]),
-            ("finish", ["k_lp_finish"]), ("d_rel", ["k_lp_rel_partial", "k_lp_rel_final"])]
     lines = ["# k_lp: decoder kernels per call", "", "Command:", "", "```", args.command, "```",
              "", "Per call, us (averages over the timed calls of each setting):", "",
-             "| setting | " + " | ".join(k for k, _ in keys) + " | total |",
-             "|---|" + "---:|" * (len(keys) + 1)]
+             "| setting | total | launches in order |", "|---|---:|---|"]
     idx = 0
     for si, setting in enumerate(LP_SETTINGS):
         reps, warm = (53, 3) if si < 6 else (13, 3)
         grp = calls[idx + warm: idx + reps]
         idx += reps
-        agg = {}
-        for c in grp:
-            for n, t in c:
-                agg[n] = agg.get(n, 0.0) + t
-        vals = [sum(agg.get(x, 0.0) for x in names) / max(len(grp), 1) for _, names in keys]
-        lines.append(f"| {setting} | " + " | ".join(f"{v:.1f}" for v in vals) +
-                     f" | {sum(vals):.1f} |")
+        if not grp:
+            continue
+        parts = [(grp[0][j][0], sum(c[j][1] for c in grp) / len(grp)) for j in range(len(grp[0]))]
+        lines.append(f"| {setting} | {sum(t for _, t in parts):.1f} | " +
+                     ", ".join(f"`{n}` {t:.1f}" for n, t in parts) + " |")
     return "\n".join(lines) + "\n"
 
 
